@@ -92,13 +92,18 @@ fe_status fe_mesh_create(const fe_mesh_desc *desc, fe_mesh **out);
 fe_status fe_mesh_destroy(fe_mesh *mesh);
 
 /* Select the implementation of the step kernel: 0 = the fastest measured
- * for the degree and precision (default); 1 = one cell x 16 vectors per
+ * for the degree and precision (default): in FP64 the tensor-product kernel,
+ * which applies the stiffness axis by axis in one launch, for blocks of three
+ * vectors or more on meshes without a zero-Neumann axis (p = 3 and 4; the
+ * other degrees from 64 cells on), as long as one z plane of a block is below
+ * 2 GiB; the kernels below elsewhere.  1 = one cell x 16 vectors per
  * workgroup, cell matrix streamed from L2 (the plain reference form);
  * 3 / 4 = one cell x 32 / 64 vectors per workgroup, so each cell-matrix
  * fragment read from L2 feeds 2 / 4 products (falls back to 1 when the block
  * would exceed the LDS); 6 = row-owner kernel (each thread loads
  * everything its outputs need in one round trip before the cell product;
- * the FP64 default for p = 1, 2 and p >= 5); 7 = persistent pipelined
+ * the FP64 default for p = 1, 2 and p >= 5 where the tensor-product kernel is
+ * not); 7 = persistent pipelined
  * row-owner kernel with the cell matrix in registers and the loads of the
  * next two items in flight during each cell product (FP64 and FP32, p <= 4;
  * else 6; BF16: 3); 9 = the pipelined kernel of 7 walking z segments of up
@@ -106,18 +111,21 @@ fe_status fe_mesh_destroy(fe_mesh *mesh);
  * two segments on a periodic z axis), the faces shared inside a segment
  * kept in LDS instead of being read and written in HBM (FP64, FP32 and BF16
  * products, p <= 4; the BF16 default at p = 4; else as 7);
- * 10 = the table kernel: the walk of 9 with the X rows copied from HBM
+ * 10 = in FP64 the tensor-product kernel (p = 3 and 4), in FP32 the table
+ * kernel: the walk of 9 with the X rows copied from HBM
  * straight into LDS two positions ahead, each position's cell read from a
  * per-segment table of first DoF and face masks built at mesh creation, and
- * the cell matrix pre-scaled by M^-1/2 (FP64 products at p = 3 and 4, FP32
- * products at p = 3, 4 and 5; no zero-Neumann axis, one leading dimension
- * for X, Y and the previous iterate, 16-byte aligned blocks with an even
- * leading dimension; applied to the whole 32-vector groups of N, the
- * columns past the last whole group run variant 9; the default wherever it
- * applies; else as 0).
+ * the cell matrix pre-scaled by M^-1/2 (products in FP32 at p = 3, 4 and 5),
+ * applied to the whole 32-vector groups of N, the columns past the last whole
+ * group running variant 9.  Both for 32 vectors or more, no zero-Neumann
+ * axis, one leading dimension for X, Y and the previous iterate, 16-byte
+ * aligned blocks with an even leading dimension (else as 1); the default in
+ * FP32 wherever it applies.
  * Variants 0, 1, 3, 4, 6 and 7 give bitwise-identical results (variant 0
- * wherever it is not variant 9 or 10); variants 9 and 10 sum each node's
- * contributions in other fixed orders (equal to rounding, reproducible).
+ * wherever it is not the tensor-product kernel, variant 9 or 10); variants 9
+ * and 10 and the tensor-product kernel sum each node's contributions in other
+ * fixed orders (equal to rounding, reproducible, each column's result
+ * independent of the columns beside it).
  * In the Bloch mode (the _k entry points at k != 0) variants 0 and 10 run
  * the table kernel with the k.G product at p = 3, 4 on the whole groups of
  * 16 complex vectors, the row-owner kernel elsewhere; the other variants

@@ -319,6 +319,7 @@ fe_status fe_mesh_create(const fe_mesh_desc *d, fe_mesh **out) {
     std::vector<double> f64s;
     std::vector<float> f32s;
     if (fold) {
+        axis_matrices(m->p, m->rule, h, m->axisM, m->axisK);
         fold_swizzle(m, m->cellA, table ? &perm : nullptr, f64s);
         f32s.assign(f64s.begin(), f64s.end());
     }
@@ -572,6 +573,7 @@ fe_status filter_step_k(fe_mesh *m, const double *X, int64_t ldx, double *Y, int
     const double kk = 0.5 * (m->kvec[0] * m->kvec[0] + m->kvec[1] * m->kvec[1]);
     StepArgs a{X, 2 * ldx, Y, 2 * ldy, Ym1, 2 * ldm, alpha, beta, shift - kk, 2 * N};
     a.S = gamma ? nullptr : m->d_Sf64;
+    a.vectors = N;
     FE_HIP(launch_step(m, a, FE_F64, s), "step kernel launch");
     if (m->nl.n_site > 0) {
         if (gamma) FE_HIP(launch_nonlocal(m, X, 2 * ldx, Y, 2 * ldy, 2 * N, alpha, s), "nonlocal kernel launch");

@@ -71,6 +71,12 @@ struct fe_mesh {
     std::vector<double> axis_coord[3];  // coordinate of each free node position
     std::vector<double> axis_mass[3];   // assembled 1-D lumped mass per free position
 
+    // with no Neumann axis: the one-dimensional cell matrices of one axis,
+    // (p + 1)^2 row-major, scaled by the per-local-index M^-1/2 of a node
+    // inside the mesh: axisM the mass, axisK the stiffness times 1/2, so that
+    // D^ (1/2 Kc) D^ is the sum of the three products of one axisK and two axisM
+    std::vector<double> axisM, axisK;
+
     // device
     // [9][maxf]: per axis a, rows a / 3 + a / 6 + a hold M^-1/2, M^-1 and M of
     // the assembled 1-D lumped mass at each free position
@@ -128,6 +134,7 @@ bool overlap(const double *a, int64_t na, int64_t Na, int64_t lda, const double 
 void gll_rule(int p, std::vector<double> &x, std::vector<double> &w);
 void ref_matrices(int p, int rule, std::vector<double> &Khat, std::vector<double> &Mhat);
 void cell_matrix_half(int p, int rule, double h, std::vector<double> &A);
+void axis_matrices(int p, int rule, double h, std::vector<double> &Ma, std::vector<double> &Ka);
 void cell_matrix_bloch(int p, int rule, double h, double kx, double ky, std::vector<double> &S);
 
 // kernels (fe_kernels.hip)
@@ -142,8 +149,13 @@ struct StepArgs {
     int64_t N;
     const double *v = nullptr;  // diagonal term of H~; null: the mesh's potential
     const double *S = nullptr;  // Bloch mode: FP64 fragments of k.G_c (interleaved complex columns)
+    int64_t vectors = 0;        // vectors the columns are (complex ones count once; 0: N)
 };
 
+// the step in tensor-product form (fe_tensor.hip), FP64
+bool tensor_applies(const fe_mesh *m, const StepArgs &a);
+bool tensor_default(const fe_mesh *m, const StepArgs &a);
+hipError_t launch_tensor(const fe_mesh *m, const StepArgs &a, hipStream_t s);
 hipError_t launch_step(const fe_mesh *m, const StepArgs &a, fe_dtype prec, hipStream_t s);
 // single-vector FP64 product in two launches (cell products, then nodal sums)
 size_t assembled_scratch_doubles(const fe_mesh *m);

@@ -2547,6 +2547,12 @@ hipError_t launch_step(const fe_mesh *m, const StepArgs &a, fe_dtype prec, hipSt
 }
 
 static hipError_t launch_step_v(const fe_mesh *m, const StepArgs &a, fe_dtype prec, hipStream_t s, int variant) {
+    // the tensor-product kernel: the FP64 default wherever it applies (see
+    // tensor_default), and variant 10 in FP64 on the blocks the table kernel
+    // would take
+    if (prec == FE_F64 && !a.S && tensor_applies(m, a) &&
+        (variant == 0 ? tensor_default(m, a) : variant == 10 && a.N >= 32 && dma_applies(m, a, prec)))
+        return launch_tensor(m, a, s);
     StepParams prm;
     prm.X = a.X; prm.ldx = a.ldx;
     prm.Y = a.Y; prm.ldy = a.ldy;

@@ -143,6 +143,26 @@ void cell_matrix_half(int p, int rule, double h, std::vector<double> &A) {
     }
 }
 
+// The one-dimensional factors of the folded cell matrix: with d_i the M^-1/2
+// factor of local index i of a node inside the mesh (its GLL mass (h/2) w_i,
+// twice that at a cell face), Ma = d (h/2 Mhat) d and Ka = d (1/2 2/h Khat) d,
+// so that D^ (1/2 Kc) D^ = Ka (x) Ma (x) Ma + Ma (x) Ka (x) Ma + Ma (x) Ma (x) Ka.
+void axis_matrices(int p, int rule, double h, std::vector<double> &Ma, std::vector<double> &Ka) {
+    std::vector<double> K, M, x, w;
+    ref_matrices(p, rule, K, M);
+    gll_rule(p, x, w);
+    const int n = p + 1;
+    std::vector<double> d(n);
+    for (int i = 0; i < n; ++i) d[i] = 1.0 / std::sqrt((i == 0 || i == p ? h : 0.5 * h) * w[i]);
+    Ma.assign(n * n, 0.0);
+    Ka.assign(n * n, 0.0);
+    for (int i = 0; i < n; ++i)
+        for (int j = 0; j < n; ++j) {
+            Ma[i * n + j] = d[i] * (0.5 * h * M[i * n + j]) * d[j];
+            Ka[i * n + j] = d[i] * (K[i * n + j] / h) * d[j];
+        }
+}
+
 }  // namespace fe
 
 namespace fe {

@@ -1,0 +1,75 @@
+"""The step kernel in tensor-product form, the FP64 default: against the
+oracle where its tiles, planes and column groups end.
+
+Tiles hold a few cells along x and y and all vectors in groups of 16; a
+workgroup walks a range of cell layers along z.  The meshes have fewer cells
+than a tile, whole tiles and remainders, every degree, Dirichlet and periodic
+axes (the halo of a tile wraps or is absent), and 1, 15, 16, 17 columns past
+the last group.  Bars as for the other FP64 kernels: 1e-13 for one product,
+1e-12 for a filter, relative per vector."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2504_00998_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+D, P = W.DIRICHLET, W.PERIODIC
+CASES = [
+    # p, cells, bc, N, ld - N
+    (1, (17, 9, 5), (P, P, D), 16, 0),
+    (1, (4, 4, 4), (D, D, D), 3, 1),
+    (2, (9, 7, 5), (P, P, P), 31, 0),
+    (2, (8, 4, 2), (D, P, D), 33, 3),
+    (3, (1, 1, 1), (D, D, D), 5, 0),
+    (3, (2, 2, 2), (P, P, P), 17, 0),
+    (3, (5, 7, 3), (P, D, P), 48, 2),
+    (4, (2, 2, 1), (P, P, D), 3, 0),
+    (4, (5, 3, 7), (P, P, D), 17, 1),
+    (4, (9, 5, 2), (D, D, P), 40, 0),
+    (5, (4, 4, 4), (P, P, D), 16, 0),
+    (5, (7, 3, 4), (D, P, P), 15, 5),
+    (6, (3, 5, 5), (P, P, D), 18, 0),
+    (6, (4, 4, 4), (D, D, D), 3, 0),
+    (7, (3, 5, 5), (P, P, D), 7, 0),
+    (7, (4, 4, 4), (P, P, P), 33, 0),
+]
+
+
+@pytest.mark.parametrize("p,cells,bc,N,pad", CASES)
+def test_tensor_kernel_matches_oracle(p, cells, bc, N, pad):
+    import paper_2504_00998_amd as fe
+    wl = W.small_slab(cells, p=p, N=N, m=6, bc=bc, **({"E": 0.0} if bc[2] == P else {}))
+    print("case: tensor", p, cells, bc, N, pad, flush=True)
+    om = O.Mesh.from_workload(wl)
+    Vq = W.workload_potential(wl, om.quad_points())
+    op = O.Operator(om, Vq, wl.E, wl.z0)
+    gm = fe.Mesh.from_workload(wl)
+    gm.set_potential(torch.from_numpy(Vq).cuda(), wl.E, wl.z0)
+    Xh = wl.X(op.n)
+    buf = torch.full((op.n, N + pad), float("nan"), dtype=torch.float64, device="cuda")
+    buf[:, :N] = torch.from_numpy(Xh).cuda()
+    out = torch.full_like(buf, float("nan"))
+    X, Y = buf[:, :N], out[:, :N]
+
+    def err(Yd, R):
+        return (np.linalg.norm(Yd.cpu().numpy() - R, axis=0) / np.linalg.norm(R, axis=0)).max()
+
+    assert err(gm.hx(X, Y), op.apply(Xh)) < 1e-13
+    first = Y.clone()
+    assert torch.equal(gm.hx(X, Y), first)
+    if op.n > N:
+        a0, b, _ = O.lanczos_bounds(op.apply, wl.lanczos_start(op.n), min(10, op.n))
+        a = O.weyl_cut(a0, b, N, op.n)
+        for a0s in (a0, math.nan):
+            assert err(gm.cheb_filter(X, wl.m, a, b, a0s, Y=Y), op.filter(Xh, wl.m, a, b, a0s)) < 1e-12
+    assert torch.isnan(out[:, N:]).all()  # the columns beside the block are left alone
+    # a column's result does not depend on the columns beside it
+    if N > 3:
+        gm.hx(X, Y)
+        part = gm.hx(X[:, 1:].contiguous())
+        assert torch.equal(part, Y[:, 1:])
