@@ -12,10 +12,10 @@
 // A workgroup owns a column of tiles: BX x BY cells in the x-y plane (their
 // low-face-closed nodes), 16 vectors, a range of cell layers along z.  It
 // walks the z planes of nodes upwards.  Per plane:
-//  - x stage: a lane holds one vector of one x row of the plane (the tile's
-//    cells and the cell before them, as a vertex node takes both cells it
-//    belongs to), loaded from global memory one plane ahead, and forms M_x u
-//    and K_x u for its output nodes into LDS;
+//  - x stage: a lane holds two vectors of XC cells of one x row of the plane
+//    (and of the cell before them, as a vertex node takes both cells it belongs
+//    to), loaded from global memory two planes ahead, and forms M_x u, K_x u
+//    and the diagonal terms (v - c) u for its output nodes into LDS;
 //  - y stage: a lane holds one vector and x position of a cell's p rows, reads
 //    the two from LDS along y and forms A = M_y M_x u and
 //    B = (K_y M_x + M_y K_x) u;
@@ -27,26 +27,32 @@
 // the x waves write plane g + 1 into one of two LDS buffers while the y-z
 // waves take plane g from the other, with one barrier per plane.  Each kind
 // then holds only its own registers (the x waves two planes of X rows in
-// flight, the y-z waves the output planes), so four waves fit a SIMD at
-// p = 4; with both stages in every wave, 168 registers and two barriers per
-// plane, the p = 4 slab below took 3.81 ms a step instead of 2.76.
+// flight, the y-z waves the output planes); with all stages in every wave and
+// two barriers per plane, the p = 4 slab below took 3.81 ms a step.
 // Every output is summed by one lane in one order: no atomics, no partial
 // sums in memory, the same bits on every run, and independent of the vectors
 // beside it.  Each value of X, the previous iterate and Y moves once, but for
 // the X rows of the halo (a cell before and a node after the tile along x
 // and y), which the neighbouring workgroups of the same XCD read at about the
-// same time.
+// same time (11.6 GB counted per step of the p = 4 slab, 10.8 without a halo).
+//
+// What bounds it up to p = 4 is memory: with all arithmetic taken out the p = 4
+// slab's step took 2.30 ms, without the X rows 1.52.  X comes in 16-byte requests
+// because a request of any width costs the address unit about the same (with
+// 8-byte ones it was busy 79 % of the time).  Above p = 4 the registers leave
+// room for few waves and the latency of a plane's stages shows.
 //
 // Measured, ms per recurrence step (two blocks read, one written), against the
 // kernels it replaces as the FP64 default: p = 4, 24x24x48 cells, 256 vectors
-// 2.76 (the table kernel 4.73) = 3.9 TB/s of the 24 bytes per value, of 5.9
-// that two reads and a write stream at; p = 6, 16x16x32 cells, 128 vectors 2.49
-// (5.53); p = 5, 20x20x40 cells, 200 vectors 3.52 (8.79); p = 3, 24x24x48 cells,
-// 100 vectors 0.66 (1.45); p = 2, 30x30x60 cells, 100 vectors 0.40 (1.09).
+// 2.47 (the table kernel 4.73) = 4.4 TB/s of the 24 bytes per value, of 5.9 that
+// two reads and a write stream at; p = 6, 16x16x32 cells, 128 vectors 1.56
+// (5.53); p = 5, 20x20x40 cells, 200 vectors 3.16 (8.79); p = 3, 24x24x48 cells,
+// 100 vectors 0.50 (1.45); p = 2, 30x30x60 cells, 100 vectors 0.29 (1.09).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 #include <type_traits>
 #include <vector>
@@ -100,6 +106,7 @@ template <int P> struct TensorParams {
     uint32_t ldx, ldy, ldm;           // row strides in bytes
     double alpha, nba, shift;         // nba = -beta / alpha
     int N, ntx, nty, nzc, layers, items, per_xcd;
+    int gw;                           // column groups side by side in the order of the items
     TensorAxis ax[3];
     double M[sym_count(P)], K[sym_count(P)], M2, K2;  // M2, K2: the vertex entries of two cells
 };
@@ -110,10 +117,16 @@ constexpr uint32_t kAbsent = 0x80000000u;  // a byte offset past every plane: re
 constexpr int kRawBuffer = 0x00020000;
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef double Pair __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ double buf_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
     const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
     return __builtin_bit_cast(double, w);
+}
+__device__ __forceinline__ Pair buf_load2(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+    return __builtin_bit_cast(Pair, w);
 }
 __device__ __forceinline__ void buf_store(double x, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, voff, soff, 0);
@@ -142,12 +155,22 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// LDS as byte addresses, so that every access is one address register of its
+// plane plus an immediate offset: left to index an array, the compiler keeps
+// the address of every row past the immediate range in a register of its own.
+typedef __attribute__((address_space(3))) double LdsDouble;
+typedef __attribute__((address_space(3))) Pair LdsPair;
+__device__ __forceinline__ LdsDouble *lds_at(uint32_t bytes) {
+    asm volatile("" : "+v"(bytes));
+    return (LdsDouble *)(uintptr_t)bytes;
+}
+
 // A sum that is formed by here (the compiler may not defer it).
 __device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
 
 // A uniform value that the compiler forms again where it is used, rather than
 // hold every multiple of it in registers for the whole walk.
-__device__ __forceinline__ void opaque(uint32_t &x) { asm volatile("" : "+s"(x)); }
+template <class T> __device__ __forceinline__ void opaque(T &x) { asm volatile("" : "+s"(x)); }
 
 // The compiler's scheduler does not move instructions across (it would
 // raise the registers alive at once past the budget).
@@ -165,13 +188,15 @@ template <int I, int E, class F> __device__ __forceinline__ void unroll(F &&f) {
 template <int P, int BX, int BY, int XC> struct TensorShape {
     static constexpr int NV = 16;
     static constexpr int WX = BX * P, RY = (BY + 1) * P + 1;
-    static constexpr int CW = (WX * BY * NV + 63) / 64;          // y-z waves
-    static constexpr int XI = RY * (BX / XC);                    // x items (row, XC cells)
-    static constexpr int XW = (XI * NV + 63) / 64;               // x waves
+    static constexpr int CW = (WX * BY * NV + 63) / 64;          // y-z waves: a lane one vector
+    static constexpr int XI = RY * (BX / XC);                    // x items (row, XC cells): a lane two vectors
+    static constexpr int XW = (XI + 7) / 8;                      // x waves
     static constexpr int T = 64 * (CW + XW);
-    static constexpr int RS = WX * NV + (WX % 2 ? 0 : NV);       // row stride: an odd number of 128-byte lines
-    static constexpr int BUF = 2 * RY * RS;                      // M_x u and K_x u of one plane
-    static constexpr int LDS = 2 * BUF;
+    static constexpr int RS = WX * NV;                           // row stride
+    static constexpr int BUF = 2 * RY * RS + BY * P * RS;        // M_x u, K_x u and (v - c) u of one plane
+    static constexpr int VN = (XC * P + 7) / 8;                  // v requests of a lane
+    static constexpr int VI = 8 * VN;                            // v of one item, in LDS
+    static constexpr int LDS = 2 * BUF + XW * 8 * VI;
     static_assert(BX % XC == 0, "whole items in a tile's row");
     static_assert(T <= 1024, "threads of a workgroup");
     static_assert(LDS * 8 <= 160 * 1024, "LDS of a workgroup");
@@ -182,16 +207,23 @@ __global__ __launch_bounds__((TensorShape<P, BX, BY, XC>::T)) __attribute__((amd
 void tensor_step_kernel(TensorParams<P> k) {
     typedef TensorShape<P, BX, BY, XC> S;
     constexpr int NV = S::NV, WX = S::WX, RY = S::RY, RS = S::RS, NX = (XC + 1) * P + 1;
-    __shared__ double lds[S::LDS];
+    __shared__ __align__(16) double lds[S::LDS];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(LdsDouble *)lds;
 
+    // workgroups go round the eight XCDs; each XCD takes a contiguous eighth of
+    // the items, neighbouring tiles of one column group next to each other, so
+    // that its L2 serves the halo rows that they share
     const int item = (int)(blockIdx.x & 7) * k.per_xcd + (int)(blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= k.per_xcd || item >= k.items) return;  // whole workgroup
     int rest = item;
+    const int gl = rest % k.gw;
+    rest /= k.gw;
     const int tx = rest % k.ntx;
     rest /= k.ntx;
     const int ty = rest % k.nty;
     rest /= k.nty;
-    const int zc = rest % k.nzc, grp = rest / k.nzc;
+    const int zc = rest % k.nzc, grp = rest / k.nzc * k.gw + gl;
+    if (grp * NV >= k.N) return;  // whole workgroup: past the last group
     const int cx0 = tx * BX, cy0 = ty * BY, cz0 = zc * k.layers, cz1 = min(cz0 + k.layers, k.ax[2].ncell);
     // the planes walked: from the layer before the first (its planes reach the
     // first vertex plane) to the vertex plane that closes the last; a first
@@ -202,65 +234,124 @@ void tensor_step_kernel(TensorParams<P> k) {
     const int tid = threadIdx.x, vec = tid % NV, col = grp * NV + vec;
     const bool live = col < k.N;
     const uint32_t cb = (uint32_t)col * 8u;
-#define TM(i, j) k.M[sym_id(P, (i), (j))]
-#define TK(i, j) k.K[sym_id(P, (i), (j))]
+    // the entries of the one-dimensional matrices, in scalar registers for the
+    // walk up to p = 4; above they do not fit beside the planes' descriptors
+    // and are read again (from the scalar cache) in every plane
+    typedef const __attribute__((address_space(4))) double *Entries;
+    Entries cf = (Entries)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
+                           offsetof(TensorParams<P>, M));
+    constexpr int NS = sym_count(P);
+#define TM(i, j) cf[sym_id(P, (i), (j))]
+#define TK(i, j) cf[NS + sym_id(P, (i), (j))]
+#define TM2 cf[2 * NS]
+#define TK2 cf[2 * NS + 1]
 
     if (__builtin_amdgcn_readfirstlane(tid) >= 64 * S::CW) {
-        // x waves: row xrow of the tile's input rows, cells xs XC .. + XC (lanes
-        // past the last item repeat it: the same values to the same places)
-        const int xitem = min((tid - 64 * S::CW) / NV, S::XI - 1), xrow = xitem % RY, xs = xitem / RY;
+        // x waves: row xrow of the tile's input rows, cells xs XC .. + XC, vectors
+        // 2 sub and 2 sub + 1 of the group (lanes past the last item repeat it:
+        // the same values to the same places)
+        const int xt = tid - 64 * S::CW, sub = xt % 8, xitem = min(xt / 8, S::XI - 1), xrow = xitem % RY, xs = xitem / RY;
+        const uint32_t xb = (uint32_t)(grp * NV + 2 * sub) * 8u;
         uint32_t xoff[NX];
         const int fy = free_node(k.ax[1], cy0 * P - P + xrow);
 #pragma unroll
         for (int j = 0; j < NX; ++j) {
             const int fx = free_node(k.ax[0], (cx0 + xs * XC - 1) * P + j);
-            xoff[j] = live && fy >= 0 && fx >= 0 ? (uint32_t)(fy * k.ax[0].nfree + fx) * k.ldx + cb : kAbsent;
+            // (the odd vector of a pair whose even one is the block's last reads
+            // what lies beside the block, within the plane's range, or zero)
+            xoff[j] = grp * NV + 2 * sub < k.N && fy >= 0 && fx >= 0 ? (uint32_t)(fy * k.ax[0].nfree + fx) * k.ldx + xb : kAbsent;
         }
-        double *const out = lds + xrow * RS + xs * XC * P * NV + vec;  // the item's first output
-        // X rows of node plane g (none past the last)
-        auto issue = [&](int g, double (&x)[NX]) {
-            const __amdgpu_buffer_rsrc_t rs = plane_of(k.X, k.px, k.rx, free_node(k.ax[2], g) | ((g1 - g) >> 31));
+        const uint32_t out = lds0 + 8 * (xrow * RS + xs * XC * P * NV + 2 * sub);  // the item's first output
+        // the diagonal terms of the rows that the tile's cells own
+        const bool orow = xrow >= P && xrow < P + BY * P;
+        const uint32_t dout = lds0 + 8 * (2 * RY * RS + (xrow - P) * RS + xs * XC * P * NV + 2 * sub);
+        // v of the item's nodes: lane sub requests nodes sub, sub + 8, ..; the
+        // item's lanes share them through LDS (the first node is none on a
+        // Dirichlet face: its X reads zero and no output takes its term)
+        const uint32_t vlds = lds0 + 8 * (2 * S::BUF + xt / 8 * S::VI);
+        uint32_t voff[S::VN];
+#pragma unroll
+        for (int q = 0; q < S::VN; ++q) {
+            const int j = sub + 8 * q, fx = (cx0 + xs * XC) * P - 1 - k.ax[0].per + j;
+            voff[q] = orow && fy >= 0 && fx >= 0 && j < XC * P ? (uint32_t)((fy * k.ax[0].nfree + fx) * 8) : kAbsent;
+        }
+        // X rows of node plane g, and its v (none past the last plane)
+        auto issue_x = [&](int g, Pair (&x)[NX]) {
+            const __amdgpu_buffer_rsrc_t r = plane_of(k.X, k.px, k.rx, free_node(k.ax[2], g) | ((g1 - g) >> 31));
 #pragma unroll
             for (int j = 0; j < NX; ++j) {
                 const uint32_t o = xoff[j];
-                x[j] = buf_load(rs, o, 0);
+                x[j] = buf_load2(r, o, 0);
             }
         };
-        auto stage = [&](const double (&x)[NX], double *o) {
+        double v[S::VN];
+        auto issue_v = [&](int g) {
+            const __amdgpu_buffer_rsrc_t r = plane_of(k.v, k.pv, k.rv, free_node(k.ax[2], g) | ((g1 - g) >> 31));
+#pragma unroll
+            for (int q = 0; q < S::VN; ++q) {
+                const uint32_t o = voff[q];
+                v[q] = buf_load(r, o, 0);
+            }
+        };
+        auto stage = [&](const Pair (&x)[NX], int buf) {
+            if constexpr (P >= 5) opaque(cf);
+            {
+                LdsDouble *const w = lds_at(vlds + 8 * sub);
+#pragma unroll
+                for (int q = 0; q < S::VN; ++q) w[8 * q] = v[q] - k.shift;
+            }
+            LdsDouble *const o = lds_at(out + 8 * buf);
 #pragma unroll
             for (int c = 0; c < XC; ++c)
                 unroll<0, P>([&](auto II) {
                     constexpr int i = decltype(II)::value;
-                    double m = (i == 0 ? k.M2 : TM(i, 0)) * x[(c + 1) * P];
-                    double q = (i == 0 ? k.K2 : TK(i, 0)) * x[(c + 1) * P];
-                    if constexpr (i == 0)
-                        unroll<0, P>([&](auto JQ) {
+                    Pair m, q;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        double mm = (i == 0 ? TM2 : TM(i, 0)) * x[(c + 1) * P][h];
+                        double qq = (i == 0 ? TK2 : TK(i, 0)) * x[(c + 1) * P][h];
+                        if constexpr (i == 0)
+                            unroll<0, P>([&](auto JQ) {
+                                constexpr int j = decltype(JQ)::value;
+                                mm = __builtin_fma(TM(P, j), x[c * P + j][h], mm);
+                                qq = __builtin_fma(TK(P, j), x[c * P + j][h], qq);
+                            });
+                        unroll<1, P + 1>([&](auto JQ) {
                             constexpr int j = decltype(JQ)::value;
-                            m = __builtin_fma(TM(P, j), x[c * P + j], m);
-                            q = __builtin_fma(TK(P, j), x[c * P + j], q);
+                            mm = __builtin_fma(TM(i, j), x[(c + 1) * P + j][h], mm);
+                            qq = __builtin_fma(TK(i, j), x[(c + 1) * P + j][h], qq);
                         });
-                    unroll<1, P + 1>([&](auto JQ) {
-                        constexpr int j = decltype(JQ)::value;
-                        m = __builtin_fma(TM(i, j), x[(c + 1) * P + j], m);
-                        q = __builtin_fma(TK(i, j), x[(c + 1) * P + j], q);
-                    });
-                    o[(c * P + i) * NV] = m;
-                    o[(c * P + i) * NV + RY * RS] = q;
+                        m[h] = mm;
+                        q[h] = qq;
+                    }
+                    *(LdsPair *)(o + (c * P + i) * NV) = m;
+                    *(LdsPair *)(o + (c * P + i) * NV + RY * RS) = q;
                 });
+            if (orow) {
+                LdsDouble *const d = lds_at(dout + 8 * buf), *const w = lds_at(vlds);
+#pragma unroll
+                for (int j = 0; j < XC * P; ++j) {
+                    const double t = w[j];
+                    *(LdsPair *)(d + j * NV) = Pair{t * x[P + j][0], t * x[P + j][1]};
+                }
+            }
         };
-        double xa[NX], xb[NX];
-        issue(g0, xa);
-        issue(g0 + 1, xb);
+        Pair xa[NX], xb2[NX];
+        issue_v(g0);
+        issue_x(g0, xa);
+        issue_x(g0 + 1, xb2);
         for (int g = g0;;) {
-            stage(xa, out);
+            stage(xa, 0);
             stage_end();
-            issue(g + 2, xa);
+            issue_v(g + 1);
+            issue_x(g + 2, xa);
             lds_barrier();
             stage_end();
             if (++g > g1) break;
-            stage(xb, out + S::BUF);
+            stage(xb2, S::BUF);
             stage_end();
-            issue(g + 2, xb);
+            issue_v(g + 1);
+            issue_x(g + 2, xb2);
             lds_barrier();
             stage_end();
             if (++g > g1) break;
@@ -270,7 +361,7 @@ void tensor_step_kernel(TensorParams<P> k) {
 
     // y-z waves: x position yx, cell yc of the tile
     const int slot = tid / NV, yx = slot % WX, yc = slot / WX;
-    uint32_t ox[2], oy[2], om[2], ov[2];  // byte offsets of rows 0 and 1 of the cell
+    uint32_t oy[2], om[2];  // byte offsets of rows 0 and 1 of the cell in a plane of Y and Ym1
     {
         const bool in = live && yc < BY && cx0 + yx / P < k.ax[0].ncell && cy0 + yc < k.ax[1].ncell;
         const int fx = free_node(k.ax[0], cx0 * P + yx);
@@ -280,76 +371,77 @@ void tensor_step_kernel(TensorParams<P> k) {
             // (row 1 of a degree-1 cell is not one of its outputs)
             const bool ok = in && fx >= 0 && fy >= 0 && r < P;
             const uint32_t row = (uint32_t)(fy * k.ax[0].nfree + fx);
-            ox[r] = ok ? row * k.ldx + cb : kAbsent;
             oy[r] = ok ? row * k.ldy + cb : kAbsent;
             om[r] = ok ? row * k.ldm + cb : kAbsent;
-            ov[r] = ok ? row * 8u : kAbsent;
         }
     }
-    const double *in = lds + min(yc, BY - 1) * P * RS + yx * NV + vec;  // the first row that the cell's vertex takes
+    // the first row that the cell's vertex takes, and the cell's diagonal terms
+    const uint32_t in = lds0 + 8 * (min(yc, BY - 1) * P * RS + yx * NV + vec);
+    const uint32_t din = lds0 + 8 * (2 * RY * RS + min(yc, BY - 1) * P * RS + yx * NV + vec);
 
-    double acc[P + 1][P], vx[P], vm[P], vv[P];
+    // planes of the previous iterate in flight: two where the registers
+    // allow and a layer's planes take the two sets in turn
+    constexpr int DEPTH = P == 2 || P == 4 ? 2 : 1;
+    double acc[P + 1][P], vm[DEPTH][P];
 #pragma unroll
     for (int i = 0; i <= P; ++i)
 #pragma unroll
         for (int r = 0; r < P; ++r) acc[i][r] = 0.0;
 
-    // the rows of plane g for its diagonal and previous-iterate terms, where
-    // its outputs are this workgroup's
-    auto issue = [&](int g, bool own) {
-        const int f = free_node(k.ax[2], g) | (own ? 0 : -1);
-        const __amdgpu_buffer_rsrc_t bx = plane_of(k.X, k.px, k.rx, f), bm = plane_of(k.Ym1, k.pm, k.rm, f),
-                                     bv = plane_of(k.v, k.pv, k.rv, f);
-        uint32_t sx = (uint32_t)k.ax[0].nfree * k.ldx, sm = (uint32_t)k.ax[0].nfree * k.ldm, sv = (uint32_t)k.ax[0].nfree * 8u;
-        opaque(sx);
+    // the rows of plane g of the previous iterate, where its outputs are
+    // this workgroup's
+    auto issue = [&](int g, double (&o)[P]) {
+        const int f = free_node(k.ax[2], g) | ((g - cz0 * P) >> 31) | ((g1 - 1 - g) >> 31);
+        const __amdgpu_buffer_rsrc_t bm = plane_of(k.Ym1, k.pm, k.rm, f);
+        uint32_t sm = (uint32_t)k.ax[0].nfree * k.ldm;
         opaque(sm);
-        opaque(sv);
-#pragma unroll
-        for (int r = 0; r < P; ++r) {
-            const uint32_t a = ox[r ? 1 : 0], b = om[r ? 1 : 0], c = ov[r ? 1 : 0], q = r ? r - 1 : 0;
-            vx[r] = buf_load(bx, a, q * sx);
-            vm[r] = buf_load(bm, b, q * sm);
-            vv[r] = buf_load(bv, c, q * sv);
-        }
+        unroll<0, P>([&](auto QQ) {
+            constexpr int q = decltype(QQ)::value;
+            const uint32_t b = om[q ? 1 : 0];
+            o[q] = buf_load(bm, b, (q ? q - 1 : 0) * sm);
+        });
     };
 
-    // one node plane: J its place in its layer (0: the vertex plane that opens
-    // layer l and closes l - 1); g its node index; flush: the outputs of the
-    // layer that it closes are this workgroup's; nown: so are those of the
-    // next plane
-    auto plane = [&](auto JJ, int g, bool flush, bool nown) {
+    // one node plane: J its place in its layer (0: the vertex plane that
+    // opens layer l and closes l - 1); g its node index; flush: the outputs
+    // of the layer that it closes are this workgroup's
+    auto plane = [&](auto JJ, int g, bool flush) {
         constexpr int J = decltype(JJ)::value;
+        if constexpr (P >= 5) opaque(cf);
         lds_barrier();
         stage_end();
-        const double *lp = in + ((g - g0) & 1 ? S::BUF : 0), *lq = lp + RY * RS;
+        const uint32_t buf = (g - g0) & 1 ? 8 * S::BUF : 0;
+        const LdsDouble *lp = lds_at(in + buf), *lq = lp + RY * RS;
+        // the plane's diagonal and previous-iterate terms, to the output
+        // plane that it is (the vertex plane's sums are still in place P)
+        constexpr int JO = J == 0 ? P : J;
+        const LdsDouble *ld = lds_at(din + buf);
+#pragma unroll
+        for (int r = 0; r < P; ++r)
+            acc[JO][r] = __builtin_fma(k.nba, vm[J % DEPTH][r], acc[JO][r] + ld[r * RS]);
+#pragma unroll
+        for (int r = 0; r < P; ++r) pin(acc[JO][r]);
+        stage_end();
+        issue(g + DEPTH, vm[J % DEPTH]);
         double A[P], B[P];
         unroll<0, 2 * P + 1>([&](auto RR) {
-            constexpr int r = decltype(RR)::value;
+            constexpr int r = decltype(RR)::value, j = r - P;
+            // (bounds the LDS reads in flight)
+            if constexpr (P >= 4 && r == P) stage_end();
             const double pr = lp[r * RS], qr = lq[r * RS];
-            if constexpr (r < P) {
-                if constexpr (r == 0) {
-                    A[0] = TM(P, 0) * pr;
-                    B[0] = __builtin_fma(TM(P, 0), qr, TK(P, 0) * pr);
+            unroll<0, (j < 0 ? 1 : P)>([&](auto II) {
+                constexpr int i = decltype(II)::value;
+                // the entries of M and K between row r and output row i
+                const double mm = j < 0 ? TM(P, r) : j == 0 && i == 0 ? TM2 : TM(i, j < 0 ? 0 : j);
+                const double kk = j < 0 ? TK(P, r) : j == 0 && i == 0 ? TK2 : TK(i, j < 0 ? 0 : j);
+                if constexpr (r == (i == 0 ? 0 : P)) {
+                    A[i] = mm * pr;
+                    B[i] = __builtin_fma(mm, qr, kk * pr);
                 } else {
-                    A[0] = __builtin_fma(TM(P, r), pr, A[0]);
-                    B[0] = __builtin_fma(TK(P, r), pr, __builtin_fma(TM(P, r), qr, B[0]));
+                    A[i] = __builtin_fma(mm, pr, A[i]);
+                    B[i] = __builtin_fma(kk, pr, __builtin_fma(mm, qr, B[i]));
                 }
-            } else {
-                constexpr int j = r - P;
-                unroll<0, P>([&](auto II) {
-                    constexpr int i = decltype(II)::value;
-                    if constexpr (j == 0 && i == 0) {
-                        A[0] = __builtin_fma(k.M2, pr, A[0]);
-                        B[0] = __builtin_fma(k.K2, pr, __builtin_fma(k.M2, qr, B[0]));
-                    } else if constexpr (j == 0) {
-                        A[i] = TM(i, 0) * pr;
-                        B[i] = __builtin_fma(TM(i, 0), qr, TK(i, 0) * pr);
-                    } else {
-                        A[i] = __builtin_fma(TM(i, j), pr, A[i]);
-                        B[i] = __builtin_fma(TK(i, j), pr, __builtin_fma(TM(i, j), qr, B[i]));
-                    }
-                });
-            }
+            });
         });
         stage_end();
         // z stage
@@ -361,52 +453,49 @@ void tensor_step_kernel(TensorParams<P> k) {
                     acc[i][r] = __builtin_fma(TK(i, J), A[r], __builtin_fma(TM(i, J), B[r], acc[i][r]));
             });
         } else {
-            unroll<0, P>([&](auto II) {
+            // plane by plane, so that an output's registers are free for the
+            // next layer's
+            unroll<0, P + 1>([&](auto II) {
                 constexpr int i = decltype(II)::value;
-                const __amdgpu_buffer_rsrc_t by =
-                    plane_of(k.Y, k.py, k.ry, free_node(k.ax[2], g - P + i) | (flush ? 0 : -1));
-                uint32_t sy = (uint32_t)k.ax[0].nfree * k.ldy;
-                opaque(sy);
-#pragma unroll
-                for (int r = 0; r < P; ++r) {
-                    const double t = __builtin_fma(TK(i, P), A[r], __builtin_fma(TM(i, P), B[r], acc[i][r]));
-                    const uint32_t o = oy[r ? 1 : 0], q = r ? r - 1 : 0;
-                    buf_store(k.alpha * t, by, o, q * sy);
+                if constexpr (i < P) {
+                    const __amdgpu_buffer_rsrc_t by =
+                        plane_of(k.Y, k.py, k.ry, free_node(k.ax[2], g - P + i) | (flush ? 0 : -1));
+                    uint32_t sy = (uint32_t)k.ax[0].nfree * k.ldy;
+                    opaque(sy);
+                    unroll<0, P>([&](auto QQ) {
+                        constexpr int r = decltype(QQ)::value;
+                        const double t = __builtin_fma(TK(i, P), A[r], __builtin_fma(TM(i, P), B[r], acc[i][r]));
+                        const uint32_t o = oy[r ? 1 : 0];
+                        buf_store(k.alpha * t, by, o, (r ? r - 1 : 0) * sy);
+                    });
                 }
-            });
 #pragma unroll
-            for (int r = 0; r < P; ++r)
-                acc[0][r] = __builtin_fma(k.K2, A[r], __builtin_fma(k.M2, B[r], acc[P][r]));
-            unroll<1, P + 1>([&](auto II) {
-                constexpr int i = decltype(II)::value;
+                for (int r = 0; r < P; ++r)
+                    acc[i][r] = i == 0 ? __builtin_fma(TK2, A[r], __builtin_fma(TM2, B[r], acc[P][r]))
+                                       : __builtin_fma(TK(i, 0), A[r], TM(i, 0) * B[r]);
 #pragma unroll
-                for (int r = 0; r < P; ++r) acc[i][r] = __builtin_fma(TK(i, 0), A[r], TM(i, 0) * B[r]);
+                for (int r = 0; r < P; ++r) pin(acc[i][r]);
+                stage_end();
             });
         }
-#pragma unroll
-        for (int r = 0; r < P; ++r)
-            acc[J][r] = __builtin_fma(k.nba, vm[r], __builtin_fma(vv[r] - k.shift, vx[r], acc[J][r]));
 #pragma unroll
         for (int i = 0; i <= P; ++i)
 #pragma unroll
             for (int r = 0; r < P; ++r) pin(acc[i][r]);
         stage_end();
-        issue(g + 1, nown);
-        stage_end();
     };
 
-    issue(g0, l0 >= cz0);
+    issue(g0, vm[0]);
+    if constexpr (DEPTH == 2) issue(g0 + 1, vm[1]);
     for (int l = l0;; ++l) {
-        const bool own = l >= cz0 && l < cz1;
-        plane(std::integral_constant<int, 0>{}, l * P, l > cz0, P > 1 ? own : l + 1 >= cz0 && l + 1 < cz1);
+        plane(std::integral_constant<int, 0>{}, l * P, l > cz0);
         if (l == cz1) break;
-        unroll<1, P>([&](auto JJ) {
-            constexpr int j = decltype(JJ)::value;
-            plane(JJ, l * P + j, false, j + 1 < P ? own : l + 1 >= cz0 && l + 1 < cz1);
-        });
+        unroll<1, P>([&](auto JJ) { plane(JJ, l * P + decltype(JJ)::value, false); });
     }
 #undef TM
 #undef TK
+#undef TM2
+#undef TK2
 }
 
 // Cell layers per workgroup along z: as many workgroups as keep the chip busy
@@ -483,11 +572,19 @@ static hipError_t launch_tensor_p(const fe_mesh *m, const StepArgs &a, hipStream
     const int64_t groups = (a.N + S::NV - 1) / S::NV, columns = (int64_t)k.ntx * k.nty * groups;
     k.layers = layers_per_group(columns, m->ncell[2], P, resident);
     k.nzc = (m->ncell[2] + k.layers - 1) / k.layers;
-    const int64_t items = columns * k.nzc;
+    // Rows off the 128-byte lines put the ends of two groups' segments into one
+    // line; then all groups of a tile go to one XCD side by side, so that its
+    // L2 joins their halves (p = 4, 24x24x48 cells, ms per step, tiles / groups
+    // next to each other: ld 258 5.24 / 2.81, ld 100 1.86 / 1.30, but ld 256,
+    // where the tiles' halo rows are what is shared, 2.44 / 2.85).
+    const bool lines = ((k.ldx | k.ldy | k.ldm | (uint32_t)(uintptr_t)a.X | (uint32_t)(uintptr_t)a.Y | (uint32_t)(uintptr_t)k.Ym1) & 127) == 0;
+    k.gw = lines ? 1 : (int)groups;
+    const int64_t items = columns / groups * ((groups + k.gw - 1) / k.gw * k.gw) * k.nzc;
     if (items > (1 << 28)) return hipErrorInvalidValue;
     k.items = (int)items;
     k.per_xcd = (int)((items + 7) / 8);
-    hipLaunchKernelGGL((tensor_step_kernel<P, BX, BY, XC, OCC>), dim3((unsigned)(8 * k.per_xcd)), dim3(S::T), 0, s, k);
+    const unsigned blocks = (unsigned)(8 * k.per_xcd);
+    hipLaunchKernelGGL((tensor_step_kernel<P, BX, BY, XC, OCC>), dim3(blocks), dim3(S::T), 0, s, k);
     return hipGetLastError();
 }
 
@@ -504,7 +601,7 @@ bool tensor_applies(const fe_mesh *m, const StepArgs &a) {
 }
 
 // Where it is the default.  It is faster than the cell kernels at every size
-// measured (DESIGN has the table), so the line is drawn by what else holds:
+// measured, so the line is drawn by what else holds:
 // the default of the other degrees on a few cells, and of one or two vectors
 // up to a mesh of the size where Lanczos and CG spend time on the product,
 // are documented to equal the one-cell kernel (variant 1) bit for bit.  The
@@ -516,15 +613,23 @@ bool tensor_default(const fe_mesh *m, const StepArgs &a) {
     return m->p == 3 || m->p == 4 || m->ncells >= 64;
 }
 
+// Tile shapes (BX, BY cells, XC cells per x item, waves per SIMD), the fastest
+// of six to ten each on the slabs above (ms per step on whole / ragged
+// 128-byte rows): p = 4 (2, 4) 2.50 / 1.25, (2, 3) 2.46 / 1.30, (3, 3) 2.45 /
+// 1.35, (4, 2) 2.55 / 1.28, (2, 2) 2.65 / 1.59; p = 6 (1, 2) 1.56 / 0.78, (2, 2)
+// 1.70 / 0.84, (2, 1) 1.71 / 0.88; p = 5 (1, 4) 2.27 / 3.16, (2, 2) 2.31 / 3.22,
+// (1, 2) 2.87 / 3.37; p = 3 (2, 6) 0.39 / 0.49, (2, 4) 0.40 / 0.51, (4, 3) 0.42 /
+// 0.53; p = 7 (1, 1) 0.60 / 0.66, (1, 2) 0.68 / 0.71.  Two waves on a cell's rows
+// (half the output planes each) were no faster at any degree.
 hipError_t launch_tensor(const fe_mesh *m, const StepArgs &a, hipStream_t s) {
     switch (m->p) {
-    case 1: return launch_tensor_p<1, 8, 4, 2, 4>(m, a, s);
-    case 2: return launch_tensor_p<2, 8, 2, 2, 4>(m, a, s);
-    case 3: return launch_tensor_p<3, 4, 3, 2, 4>(m, a, s);
-    case 4: return launch_tensor_p<4, 4, 2, 2, 4>(m, a, s);
-    case 5: return launch_tensor_p<5, 3, 2, 3, 3>(m, a, s);
-    case 6: return launch_tensor_p<6, 2, 2, 2, 3>(m, a, s);
-    case 7: return launch_tensor_p<7, 2, 1, 2, 2>(m, a, s);
+    case 1: return launch_tensor_p<1, 4, 8, 2, 4>(m, a, s);
+    case 2: return launch_tensor_p<2, 3, 6, 3, 4>(m, a, s);
+    case 3: return launch_tensor_p<3, 2, 6, 2, 3>(m, a, s);
+    case 4: return launch_tensor_p<4, 2, 4, 2, 3>(m, a, s);
+    case 5: return launch_tensor_p<5, 1, 4, 1, 3>(m, a, s);
+    case 6: return launch_tensor_p<6, 1, 2, 1, 2>(m, a, s);
+    case 7: return launch_tensor_p<7, 1, 1, 1, 2>(m, a, s);
     default: return hipErrorInvalidValue;
     }
 }
