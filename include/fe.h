@@ -127,9 +127,9 @@ fe_status fe_mesh_destroy(fe_mesh *mesh);
  * fixed orders (equal to rounding, reproducible, each column's result
  * independent of the columns beside it).
  * In the Bloch mode (the _k entry points at k != 0) variants 0 and 10 run
- * the table kernel with the k.G product at p = 3, 4 on the whole groups of
- * 16 complex vectors, the row-owner kernel elsewhere; the other variants
- * run the row-owner kernel.
+ * the tensor-product kernel with the k.G term, at every degree, where it
+ * applies (no zero-Neumann axis, a plane below 2 GiB); the row-owner kernel
+ * there and for the other variants.
  * Variants 2 (register-resident), 5 (tiles of cells) and 8
  * (warp-specialised), slower than the defaults everywhere, were removed:
  * FE_EINVAL for them and for values outside 0..10. */

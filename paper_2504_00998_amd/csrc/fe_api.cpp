@@ -196,18 +196,15 @@ static void free_mesh(fe_mesh *m) {
     (void)hipFree(m->d_axis);
     (void)hipFree(m->d_zcoord);
     (void)hipFree(m->d_Af64);
-    (void)hipFree(m->d_Af64s);
     (void)hipFree(m->d_Af32s);
     (void)hipFree(m->d_tabperm);
     (void)hipFree(m->d_zero);
     (void)hipFree(m->d_segtab);
-    (void)hipFree(m->d_segtab1);
     (void)hipFree(m->d_Af32);
     (void)hipFree(m->d_Abf16);
     (void)hipFree(m->d_v);
     (void)hipFree(m->d_wrel);
     (void)hipFree(m->d_Sf64);
-    (void)hipFree(m->d_Sf64s);
     (void)hipFree(m->d_scratch);
     nonlocal_release(m);
     if (m->blas) rocblas_destroy_handle(static_cast<rocblas_handle>(m->blas));
@@ -315,21 +312,16 @@ fe_status fe_mesh_create(const fe_mesh_desc *d, fe_mesh **out) {
     const bool table = fold && m->p >= 3 && m->p <= 5 && m->n < INT32_MAX;
     std::vector<int32_t> perm;
     if (table) build_table_row_perm(m->p, table_tiles_per_wave(m->p), perm);
-    m->tab_perm = perm;
     std::vector<double> f64s;
     std::vector<float> f32s;
     if (fold) {
-        axis_matrices(m->p, m->rule, h, m->axisM, m->axisK);
+        axis_matrices(m->p, m->rule, h, m->axisM, m->axisK, m->axisG);
         fold_swizzle(m, m->cellA, table ? &perm : nullptr, f64s);
         f32s.assign(f64s.begin(), f64s.end());
     }
     const double zeros[32] = {};
-    std::vector<int32_t> segtab, segtab1;
-    if (table) {
-        build_segment_table(m, 2, segtab, m->seg_off, m->seg_zl, m->seg_bx, m->seg_by);
-        int zl1 = 1, bx1 = 1, by1 = 1;
-        if (m->seg_by > 1) build_segment_table(m, 1, segtab1, m->seg_off1, zl1, bx1, by1);
-    }
+    std::vector<int32_t> segtab;
+    if (table) build_segment_table(m, segtab, m->seg_off, m->seg_zl, m->seg_bx);
 
     auto up = [&](void **dst, const void *src, size_t bytes) -> bool {
         if (hipMalloc(dst, bytes) != hipSuccess) return false;
@@ -339,11 +331,9 @@ fe_status fe_mesh_create(const fe_mesh_desc *d, fe_mesh **out) {
               up((void **)&m->d_zcoord, m->axis_coord[2].data(), m->axis_coord[2].size() * sizeof(double)) &&
               up((void **)&m->d_wrel, wrel.data(), wrel.size() * sizeof(double)) &&
               up((void **)&m->d_Af64, f64.data(), f64.size() * sizeof(double)) &&
-              (!fold || up((void **)&m->d_Af64s, f64s.data(), f64s.size() * sizeof(double))) &&
               (!fold || up((void **)&m->d_Af32s, f32s.data(), f32s.size() * sizeof(float))) &&
               up((void **)&m->d_zero, zeros, sizeof(zeros)) &&
               (segtab.empty() || up((void **)&m->d_segtab, segtab.data(), segtab.size() * sizeof(int32_t))) &&
-              (segtab1.empty() || up((void **)&m->d_segtab1, segtab1.data(), segtab1.size() * sizeof(int32_t))) &&
               (perm.empty() || up((void **)&m->d_tabperm, perm.data(), perm.size() * sizeof(int32_t))) &&
               up((void **)&m->d_Af32, f32.data(), f32.size() * sizeof(float)) &&
               up((void **)&m->d_Abf16, bf.data(), bf.size() * sizeof(uint16_t)) &&
@@ -522,25 +512,15 @@ fe_status fe_set_kpoint(fe_mesh *m, double kx, double ky) {
     FE_HIP(hipDeviceSynchronize(), "hipDeviceSynchronize");
     const double old[2] = {m->kvec[0], m->kvec[1]};
     if (kx != 0.0 || ky != 0.0) {
-        std::vector<double> S, f, fs;
+        std::vector<double> S, f;
         cell_matrix_bloch(m->p, m->rule, m->h, kx, ky, S);
         swizzle_f64(m, S, f);
-        // the table kernel's copy (FP64 at p = 3, 4): folded, rows in its order
-        const bool table = m->d_Af64s && !m->tab_perm.empty() && m->p <= 4;
-        if (table) fold_swizzle(m, S, &m->tab_perm, fs);
         if (!m->d_Sf64 && hipMalloc(&m->d_Sf64, f.size() * sizeof(double)) != hipSuccess) {
             (void)hipGetLastError();
             m->d_Sf64 = nullptr;
             return fail(FE_ENOMEM, "device allocation failed in fe_set_kpoint");
         }
-        if (table && !m->d_Sf64s && hipMalloc(&m->d_Sf64s, fs.size() * sizeof(double)) != hipSuccess) {
-            (void)hipGetLastError();
-            m->d_Sf64s = nullptr;
-            return fail(FE_ENOMEM, "device allocation failed in fe_set_kpoint");
-        }
         FE_HIP(hipMemcpy(m->d_Sf64, f.data(), f.size() * sizeof(double), hipMemcpyHostToDevice), "hipMemcpy");
-        if (table)
-            FE_HIP(hipMemcpy(m->d_Sf64s, fs.data(), fs.size() * sizeof(double), hipMemcpyHostToDevice), "hipMemcpy");
     }
     m->kvec[0] = kx;
     m->kvec[1] = ky;

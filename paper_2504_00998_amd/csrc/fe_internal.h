@@ -74,8 +74,9 @@ struct fe_mesh {
     // with no Neumann axis: the one-dimensional cell matrices of one axis,
     // (p + 1)^2 row-major, scaled by the per-local-index M^-1/2 of a node
     // inside the mesh: axisM the mass, axisK the stiffness times 1/2, so that
-    // D^ (1/2 Kc) D^ is the sum of the three products of one axisK and two axisM
-    std::vector<double> axisM, axisK;
+    // D^ (1/2 Kc) D^ is the sum of the three products of one axisK and two
+    // axisM; axisG the advection matrix (the k.G term of the Bloch mode)
+    std::vector<double> axisM, axisK, axisG;
 
     // device
     // [9][maxf]: per axis a, rows a / 3 + a / 6 + a hold M^-1/2, M^-1 and M of
@@ -86,30 +87,24 @@ struct fe_mesh {
     double *d_Af64 = nullptr;     // swizzled A fragments of 1/2 Kc (f64)
     // with no Neumann axis every free node's M^-1/2 is the product of per-axis
     // factors that depend only on its local index in any cell containing it,
-    // so D Kc D folds into one cell matrix: swizzled f64 fragments of
-    // D^ (1/2 Kc) D^ (null with a Neumann axis), and the same rounded to f32;
-    // where the table kernel applies (p = 3, 4, 5) their rows are in the
-    // order of d_tabperm (row r: local node d_tabperm[r], -1 a zero row)
-    double *d_Af64s = nullptr;
+    // so D Kc D folds into one cell matrix: swizzled fragments of
+    // D^ (1/2 Kc) D^ rounded to f32 (null with a Neumann axis), their rows in
+    // the order of d_tabperm where the table kernel applies (p = 3, 4, 5; row
+    // r: local node d_tabperm[r], -1 a zero row)
     float *d_Af32s = nullptr;
     int32_t *d_tabperm = nullptr;
-    std::vector<int32_t> tab_perm;  // its host copy
     double *d_zero = nullptr;     // 32 zero doubles (source of padded / absent rows)
     // segment table of the table kernel (p = 3, 4, 5 with the folded cell
     // matrix): per colour pass, per z segment, first DoF and face masks
     int32_t *d_segtab = nullptr;
     std::vector<int64_t> seg_off;  // entries of colour pass c: [seg_off[c], seg_off[c+1])
-    // the same for bricks one cell deep in y, where seg_by > 1 (else null)
-    int32_t *d_segtab1 = nullptr;
-    std::vector<int64_t> seg_off1;
-    int seg_zl = 1, seg_bx = 1, seg_by = 1;  // cells of a brick along z, x and y
+    int seg_zl = 1, seg_bx = 1;  // cells of a brick along z and x
     float *d_Af32 = nullptr;      // f32
     uint16_t *d_Abf16 = nullptr;  // bf16 bits
     double *d_v = nullptr;        // [n] diagonal potential term of H~
     double *d_wrel = nullptr;     // [3][p+1]: (h/2) w_i per axis (for v and Vbar)
     double kvec[2] = {0.0, 0.0};  // Bloch wave vector (k_x, k_y) of the complex entry points
     double *d_Sf64 = nullptr;     // swizzled FP64 fragments of k.G_c (null while k = 0)
-    double *d_Sf64s = nullptr;    // the same folded as d_Af64s, for the table kernel (p = 3, 4)
     bool potential_set = false;
     int kernel_variant = 0;  // 0: fastest available, 1: generic colour-pass kernel
     double E = 0.0, z0 = 0.0;
@@ -134,7 +129,8 @@ bool overlap(const double *a, int64_t na, int64_t Na, int64_t lda, const double 
 void gll_rule(int p, std::vector<double> &x, std::vector<double> &w);
 void ref_matrices(int p, int rule, std::vector<double> &Khat, std::vector<double> &Mhat);
 void cell_matrix_half(int p, int rule, double h, std::vector<double> &A);
-void axis_matrices(int p, int rule, double h, std::vector<double> &Ma, std::vector<double> &Ka);
+void axis_matrices(int p, int rule, double h, std::vector<double> &Ma, std::vector<double> &Ka,
+                   std::vector<double> &Ga);
 void cell_matrix_bloch(int p, int rule, double h, double kx, double ky, std::vector<double> &S);
 
 // kernels (fe_kernels.hip)
@@ -203,8 +199,7 @@ void fold_swizzle(const fe_mesh *m, const std::vector<double> &A, const std::vec
                   std::vector<double> &f64);
 // segment table, output-row order and row tiles per wave of the table
 // kernel (fe_kernels.hip)
-void build_segment_table(const fe_mesh *m, int by_most, std::vector<int32_t> &tab, std::vector<int64_t> &off,
-                         int &zl, int &bx, int &by);
+void build_segment_table(const fe_mesh *m, std::vector<int32_t> &tab, std::vector<int64_t> &off, int &zl, int &bx);
 void build_table_row_perm(int p, int tiles_per_wave, std::vector<int32_t> &perm);
 int table_tiles_per_wave(int p);
 void nonlocal_release(fe_mesh *m);

@@ -1728,20 +1728,16 @@ static hipError_t launch_pipe_p(StepParams prm, const fe_mesh *m, hipStream_t s)
 }
 
 // ------------------------------------------------------------------------
-// Step kernel with direct-to-LDS prefetch and a brick table (p = 3, 4, and
-// p = 5 with FP32 products; meshes without a zero-Neumann axis, where M^-1/2
-// of a free node depends
-// only on its local index and folds into the cell matrix:
-// A' = D^ (1/2 Kc) D^), with FP64 cell products (PREC 0) or FP32 ones
-// (PREC 1: A' rounded to FP32, each X element rounded to FP32 as the
-// product reads it from the FP64 buffer, FP32 accumulation; everything
-// else, the buffers and the epilogue, in FP64 as for PREC 0).
+// Step kernel with direct-to-LDS prefetch and a brick table (FP32 cell
+// products at p = 3, 4 and 5; meshes without a zero-Neumann axis, where M^-1/2
+// of a free node depends only on its local index and folds into the cell
+// matrix: A' = D^ (1/2 Kc) D^, rounded to FP32; each X element is rounded to
+// FP32 as the product reads it from the FP64 buffer, FP32 accumulation;
+// everything else, the buffers and the epilogue, in FP64).
 //
-// On gfx950 the FP64 4x4x4 MFMA and every other vector instruction share the
-// SIMD's vector ALU (an FP64 MFMA holds it as long as 16 wave-wide FMA
-// instructions would), and a wave issues about one instruction per four
-// cycles, so every instruction a wave spends per cell position besides its
-// products is taken from them.  This kernel keeps that count small:
+// A wave issues about one instruction per four cycles, so every instruction it
+// spends per cell position besides its products is taken from them and from
+// its requests.  This kernel keeps that count small:
 // - the X rows go from HBM straight into LDS with 16-byte global-to-LDS
 //   requests, two positions ahead, into three LDS buffers (no staging
 //   arithmetic; with the folded cell matrix they need no scaling);
@@ -1753,10 +1749,10 @@ static hipError_t launch_pipe_p(StepParams prm, const fe_mesh *m, hipStream_t s)
 //   (minus a per-lane wrap correction where the mask says so), and its
 //   first-writer and validity tests are its per-lane face bits against those
 //   masks: no per-row index arithmetic, no colour logic, no divisions.
-// Persistent workgroups walk the items (brick of BX x BY x zl cells, 32
+// Persistent workgroups walk the items (brick of BX x 1 x zl cells, 32
 // vectors (16 at p = 5); the launcher hands the columns past the last whole
 // group to another kernel) of a colour with stride gridDim.x, cell by cell
-// (x fastest, then y, then z), one wave per 16-row tile of A' with the
+// (x fastest, then z), one wave per 16-row tile of A' with the
 // tile's fragments in registers.  A position's old values and v are
 // loaded to registers at its start and used after its product; the partial
 // sums of a brick's inner faces pass from cell to cell through LDS holds
@@ -1858,46 +1854,35 @@ template <int P> struct TabRow {
 };
 
 // Shapes of the table kernel: one 16-row tile of A' per wave; p = 3, 4: 4 / 8
-// tiles and 32 vectors per item; with FP32 products at p = 4 two waves per
-// tile, one 16-vector group each (16 waves, up to 4 per SIMD within 128
-// registers: 3-5 % faster than one wave per tile; no faster at p = 3; with
-// FP64 products the same split spills at 128 registers and was 4.7 %
-// slower); p = 5 (FP32
-// products only: 224 padded rows): 14 waves (up to 4 per SIMD; 56 fragment
-// registers each) and 16 vectors per item, so that three X buffers of 224
-// rows fit the LDS (7 waves of two tiles each, 2 per SIMD, were 7 % slower)
-template <int P, int PREC = 0> struct TabCfg {
-    static constexpr int TPW = 1, G = P == 5 ? 1 : 2, GS = (PREC == 1 && P == 4) ? 2 : 1;
+// tiles and 32 vectors per item; at p = 4 two waves per tile, one 16-vector
+// group each (16 waves, up to 4 per SIMD within 128 registers: 3-5 % faster
+// than one wave per tile; no faster at p = 3); p = 5 (224 padded rows): 14 waves
+// (up to 4 per SIMD; 56 fragment registers each) and 16 vectors per item, so
+// that three X buffers of 224 rows fit the LDS (7 waves of two tiles each, 2 per
+// SIMD, were 7 % slower)
+template <int P> struct TabCfg {
+    static constexpr int TPW = 1, G = P == 5 ? 1 : 2, GS = P == 4 ? 2 : 1;
 };
 
 // (at most 2 waves per SIMD, or as many as the workgroup puts on one)
-// CPX (FP64 only): the Bloch-k mode, columns complex vectors stored as
-// interleaved (re, im) pairs; the operator gains -i D^ (k.G_c) D^ (folded
-// fragments in k.S, rows in the same order as k.A).  As -i S (x_r + i x_i) =
-// S x_i - i S x_r, each k-step adds S times the lane's im column to its re
-// accumulator and S times the negated re column (the product's B-operand
-// negation) to its im accumulator.
 // GS waves per row tile, each taking NGRP / GS of the item's 16-vector groups
 // (GS = 2: twice the waves, each with half the accumulators and requests).
-template <int P, int PREC, int TPW, int NGRP, int BX, int BY, bool CPX = false, int GS = 1>
+template <int P, int TPW, int NGRP, int BX, int GS = 1>
 __global__ __launch_bounds__((64 * GS * TabShape<P, TPW, NGRP>::W))
 __attribute__((amdgpu_waves_per_eu(1, GS * TabShape<P, TPW, NGRP>::W > 8 ? (GS * TabShape<P, TPW, NGRP>::W + 3) / 4 : 2)))
 void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *__restrict__ rowperm, int64_t nitems) {
-    static_assert(PREC == 0 || PREC == 1, "FP64 or FP32 cell products");
-    static_assert(!CPX || PREC == 0, "the Bloch mode is FP64 only");
-    typedef typename FragOf<PREC>::T AT;
+    typedef float AT;
     typedef TabShape<P, TPW, NGRP> S;
     static_assert(NGRP % GS == 0, "groups split evenly over a tile's waves");
     // GI groups per item, G per wave
     constexpr int N1 = P + 1, NKS = S::NKS, GI = S::G, G = GI / GS, XS = S::XS, W = S::W, NDMA = 2 * TPW * G;
     // LDS holds (doubles), each node once: the x face between consecutive
-    // cells of a brick row (N1 x N1 nodes), the back faces of a brick row
-    // ((BX p + 1) x N1 nodes: x by z), the top faces of a brick layer
-    // ((BX p + 1) x (BY p + 1) nodes: x by y); each slot is read and written
-    // at one position by two rows of the same wave (see build_table_row_perm)
+    // cells of a brick row (N1 x N1 nodes), the top faces of a brick layer
+    // ((BX p + 1) x N1 nodes: x by y); each slot is read and written at one
+    // position by two rows of the same wave (see build_table_row_perm)
     constexpr int ZW = BX * P + 1, V = 16 * GI;
-    constexpr int XHS = BX > 1 ? N1 * N1 * V : 0, YHS = BY > 1 ? ZW * N1 * V : 0, ZHS = ZW * (BY * P + 1) * V;
-    constexpr int YH0 = XHS, ZH0 = YH0 + YHS, ZERO0 = ZH0 + ZHS;
+    constexpr int XHS = BX > 1 ? N1 * N1 * V : 0, ZHS = ZW * N1 * V;
+    constexpr int ZH0 = XHS, ZERO0 = ZH0 + ZHS;
     // three X buffers [G][NCP][16] as distinct arrays, each named at compile
     // time by the position it serves, so that the compiler sees that a
     // product's LDS reads and the X requests in flight touch different
@@ -1918,68 +1903,57 @@ void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *_
     const int stride = (int)gridDim.x;
     const int sdiv = stride / ngroups, smod = stride % ngroups;
     const int zl = k.zl;
-    const int npos = (int)((nitems - 1 - blockIdx.x) / stride + 1) * zl * BX * BY;  // < 2^31, as items per launch
-    const int ystep = P * (int)k.nfx, zstep = P * (int)(k.nfx * k.nfy);  // DoF steps to the next cell along y, z
+    const int npos = (int)((nitems - 1 - blockIdx.x) / stride + 1) * zl * BX;  // < 2^31, as items per launch
+    const int zstep = P * (int)(k.nfx * k.nfy);  // DoF step to the next cell along z
     const int64_t ld = k.ldx;  // one leading dimension for X, Y and the previous iterate
-    // the wave's row tiles of A' (tiles wave + W j), and in the Bloch mode
-    // of S', resident for the launch
-    AT ar[TPW][NKS], sr[CPX ? TPW : 1][CPX ? NKS : 1];
+    // the wave's row tiles of A' (tiles wave + W j), resident for the launch
+    AT ar[TPW][NKS];
 #pragma unroll
     for (int j = 0; j < TPW; ++j) {
         const AT *A = reinterpret_cast<const AT *>(k.A) + (size_t)(wave + W * j) * NKS * 64 + lane;
 #pragma unroll
         for (int s = 0; s < NKS; ++s) ar[j][s] = A[s * 64];
-        if constexpr (CPX) {
-            const double *Sf = k.S + (size_t)(wave + W * j) * NKS * 64 + lane;
-#pragma unroll
-            for (int s = 0; s < NKS; ++s) sr[j][s] = Sf[s * 64];
-        }
     }
     // per tile: the node whose output row this lane's accumulators hold
     // (row pipe_row of the tile, vectors vq + pipe_off(q) of each 16-vector
     // group; the rows of A' are the cell's nodes in the order rowperm gives)
     // and the two rows it requests X for (rows 16 tile + 8 h + l / 8, in
     // node order, vectors 2 (l % 8) + {0, 1} of each group)
-    const int vq = pipe_vec<PREC>(lane);
+    const int vq = pipe_vec<1>(lane);
     TabRow<P> R[TPW], Q[TPW][2];
-    int xo[TPW], xh[TPW], yh[TPW], zh[TPW];  // offsets in an X buffer and in the three holds
+    int xo[TPW], xh[TPW], zh[TPW];  // offsets in an X buffer and in the two holds
 #pragma unroll
     for (int j = 0; j < TPW; ++j) {
-        const int tile = wave + W * j, node = rowperm[16 * tile + pipe_row<PREC>(lane)];
+        const int tile = wave + W * j, node = rowperm[16 * tile + pipe_row<1>(lane)];
         R[j].init(k, node < 0 ? N1 * N1 * N1 : node, vq);
         Q[j][0].init(k, 16 * tile + (lane >> 3), 2 * (lane & 7));
         Q[j][1].init(k, 16 * tile + 8 + (lane >> 3), 2 * (lane & 7));
         const int l = node < 0 ? 0 : node, i = l % N1, jy = (l / N1) % N1, kk = l / (N1 * N1);
         xo[j] = l * 16 + vq;
         xh[j] = (jy + N1 * kk) * V + vq;
-        yh[j] = YH0 + (i + ZW * kk) * V + vq;
         zh[j] = ZH0 + (i + ZW * jy) * V + vq;
     }
     const double *ob = k.Ym1 ? k.Ym1 : k.X;
     const double nbeta = k.Ym1 ? -k.beta : 0.0;
 
     // a walk position: brick s of the colour, vector group grp, cell
-    // (bx, by, c) of the brick (bx along x, fastest; by along y; c along z);
-    // e its table entry
+    // (bx, c) of the brick (bx along x, fastest; c along z); e its table entry
     struct Pos {
-        int s, grp, c, bx, by;
+        int s, grp, c, bx;
         int2 e;
     };
     auto advance = [&](Pos p) {
         if (++p.bx == BX) {
             p.bx = 0;
-            if (++p.by == BY) {
-                p.by = 0;
-                if (++p.c == zl) {
-                    p.c = 0;
-                    p.s += sdiv;
-                    p.grp += smod;
-                    if (p.grp >= ngroups) {
-                        p.grp -= ngroups;
-                        ++p.s;
-                    }
-                    p.e = segtab[p.s];
+            if (++p.c == zl) {
+                p.c = 0;
+                p.s += sdiv;
+                p.grp += smod;
+                if (p.grp >= ngroups) {
+                    p.grp -= ngroups;
+                    ++p.s;
                 }
+                p.e = segtab[p.s];
             }
         }
         return p;
@@ -1993,10 +1967,10 @@ void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *_
     };
     auto cell = [&](const Pos &p) {
         Cell q;
-        q.I0 = p.e.x + p.bx * P + p.by * ystep + p.c * zstep;
+        q.I0 = p.e.x + p.bx * P + p.c * zstep;
         q.U = (int64_t)q.I0 * ld + (int64_t)p.grp * GI * 16 + g0 * 16;
-        const int hi = (p.bx == BX - 1 ? 2 : 0) | (p.by == BY - 1 ? 8 : 0) | (p.c == zl - 1 ? 32 : 0);
-        const int m = hi | (p.bx == 0 ? 1 : 0) | (p.by == 0 ? 4 : 0) | (p.c == 0 ? 16 : 0);
+        const int hi = (p.bx == BX - 1 ? 2 : 0) | 8 | (p.c == zl - 1 ? 32 : 0);
+        const int m = hi | (p.bx == 0 ? 1 : 0) | 4 | (p.c == 0 ? 16 : 0);
         q.fm = (p.e.y >> SEG_FM) & m;
         q.dm = (p.e.y >> SEG_DM) & m;
         q.wm = (p.e.y >> SEG_WM) & hi;
@@ -2061,7 +2035,7 @@ void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *_
         const Cell e = cell(cur);
         const bool slow = (e.dm | e.wm) != 0;  // uniform
         int64_t E[TPW];
-        bool valid[TPW], fst[TPW], left[TPW], right[TPW], front[TPW], back[TPW], bot[TPW], top[TPW];
+        bool valid[TPW], fst[TPW], left[TPW], right[TPW], bot[TPW], top[TPW];
         double vraw[TPW], o[TPW][G][4];
 #pragma unroll
         for (int j = 0; j < TPW; ++j) {
@@ -2076,15 +2050,12 @@ void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *_
                 valid[j] = (R[j].faces & (e.dm | 64)) == 0;
             }
             // faces shared with the brick's previous / next cell along x
-            // (the x-face hold), along y (the back-face hold) and along z
-            // (the top-face hold)
+            // (the x-face hold) and along z (the top-face hold)
             left[j] = BX > 1 && (R[j].faces & 1) != 0 && cur.bx > 0;
             right[j] = BX > 1 && (R[j].faces & 2) != 0 && cur.bx < BX - 1;
-            front[j] = BY > 1 && (R[j].faces & 4) != 0 && cur.by > 0;
-            back[j] = BY > 1 && (R[j].faces & 8) != 0 && cur.by < BY - 1;
             bot[j] = (R[j].faces & 16) != 0 && cur.c > 0;
             top[j] = (R[j].faces & 32) != 0 && cur.c < zl - 1;
-            const bool held = left[j] || front[j] || bot[j];
+            const bool held = left[j] || bot[j];
             fst[j] = valid[j] && (R[j].faces & e.fm) == 0 && !held;
             // old values: the previous iterate for a first writer, else Y
             // (an earlier colour has written the node); none for rows off the
@@ -2106,47 +2077,7 @@ void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *_
         n2 = t + 2 < npos ? advance(n1) : n1;
         prefetch(cell(n2), xn);
         double acc[TPW][G][4];
-        if constexpr (PREC == 0) {
-#pragma unroll
-            for (int j = 0; j < TPW; ++j)
-#pragma unroll
-                for (int g = 0; g < G; ++g)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) acc[j][g][q] = 0.0;
-            double bc[G][4], bn[G][4];
-#pragma unroll
-            for (int g = 0; g < G; ++g) f64_pair_b(xs + (g0 + g) * XS, 0, lane, bc[g]);
-#pragma unroll
-            for (int s = 0; s < NKS; ++s) {
-                if (s + 1 < NKS)
-#pragma unroll
-                    for (int g = 0; g < G; ++g) f64_pair_b(xs + (g0 + g) * XS, s + 1, lane, bn[g]);
-#pragma unroll
-                for (int j = 0; j < TPW; ++j)
-#pragma unroll
-                    for (int g = 0; g < G; ++g)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            acc[j][g][q] = __builtin_amdgcn_mfma_f64_4x4x4f64(ar[j][s], bc[g][q], acc[j][g][q], 0, 0, 0);
-                if constexpr (CPX) {
-                    // columns q = 0, 2 are re, q = 1, 3 the im of the same
-                    // complex vectors; the last argument 2 negates B
-#pragma unroll
-                    for (int j = 0; j < TPW; ++j)
-#pragma unroll
-                        for (int g = 0; g < G; ++g) {
-                            acc[j][g][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(sr[j][s], bc[g][1], acc[j][g][0], 0, 0, 0);
-                            acc[j][g][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(sr[j][s], bc[g][0], acc[j][g][1], 0, 0, 2);
-                            acc[j][g][2] = __builtin_amdgcn_mfma_f64_4x4x4f64(sr[j][s], bc[g][3], acc[j][g][2], 0, 0, 0);
-                            acc[j][g][3] = __builtin_amdgcn_mfma_f64_4x4x4f64(sr[j][s], bc[g][2], acc[j][g][3], 0, 0, 2);
-                        }
-                }
-#pragma unroll
-                for (int g = 0; g < G; ++g)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) bc[g][q] = bn[g][q];
-            }
-        } else {
+        {
             // transposed 16x16x4 products: the X slice (row 4s + l / 16,
             // vector pipe_perm(l % 16), rounded from the buffer's f64 to f32)
             // first, the fragment second; lane l's accumulator q then holds
@@ -2193,14 +2124,13 @@ void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *_
 #pragma unroll
                 for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(o[j][g][q]));
         }
-        // this cell's offsets in the back-face hold (x) and the top-face hold (x, y)
-        const int yoff = cur.bx * P * V, zoff = yoff + cur.by * P * ZW * V;
+        // this cell's offset in the top-face hold (x)
+        const int zoff = cur.bx * P * V;
         // epilogue, one form for every row:
         //   out = alpha acc + (s x + (gamma o + h))
         // first writer: s = alpha (v - c), gamma = -beta, h = 0 (x raw from
         // the buffer); a row whose partial sum a hold carries (from the
-        // previous cell along x, else along y, else along z): s = 0, o = 0,
-        // h = the hold; any other row: s = 0, gamma = 1, h = 0.  Every hold
+        // previous cell along x, else along z): s = 0, o = 0, h = the hold; any other row: s = 0, gamma = 1, h = 0.  Every hold
         // read of the wave comes before its hold writes (a slot read at this
         // position is written at it only by a row of the same wave).
         double out[TPW][G][4];
@@ -2208,7 +2138,7 @@ void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *_
         for (int j = 0; j < TPW; ++j) {
             const double sl = fst[j] ? k.alpha * (vraw[j] - k.shift) : 0.0;
             const double gl = fst[j] ? nbeta : 1.0;
-            const int hoff = left[j] ? xh[j] : front[j] ? yh[j] + yoff : bot[j] ? zh[j] + zoff : ZERO0;
+            const int hoff = left[j] ? xh[j] : bot[j] ? zh[j] + zoff : ZERO0;
             const double *hrow = hd + hoff;
 #pragma unroll
             for (int g = 0; g < G; ++g) {
@@ -2226,10 +2156,10 @@ void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *_
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int j = 0; j < TPW; ++j) {
-            // the partial sum goes on to the next cell along x, else along y,
-            // else along z, else to Y
-            if (right[j] || back[j] || top[j]) {
-                double *h = hd + (right[j] ? xh[j] : back[j] ? yh[j] + yoff : zh[j] + zoff);
+            // the partial sum goes on to the next cell along x, else along z,
+            // else to Y
+            if (right[j] || top[j]) {
+                double *h = hd + (right[j] ? xh[j] : zh[j] + zoff);
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
                     lds_store16(h + 16 * (g0 + g), out[j][g][0], out[j][g][1]);
@@ -2260,7 +2190,6 @@ void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *_
         p0.grp = it % ngroups;
         p0.c = 0;
         p0.bx = 0;
-        p0.by = 0;
         p0.e = segtab[p0.s];
     }
     p1 = npos > 1 ? advance(p0) : p0;
@@ -2280,7 +2209,7 @@ void step_tab_kernel(StepParams k, const int2 *__restrict__ segtab, const int *_
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 }
 
-template <int P, int PREC, int TPW, int G, int BX, int BY, bool CPX, int GS>
+template <int P, int TPW, int G, int BX, int GS>
 static hipError_t launch_tab_p(StepParams prm, const fe_mesh *m, hipStream_t s) {
     typedef TabShape<P, TPW, G> S;
     constexpr int W = GS * S::W;
@@ -2289,7 +2218,7 @@ static hipError_t launch_tab_p(StepParams prm, const fe_mesh *m, hipStream_t s) 
     if (!attr) {
         int per_cu = 0, dev = 0, cus = 0;
         hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void *>(&step_tab_kernel<P, PREC, TPW, G, BX, BY, CPX, GS>), 64 * W, 0);
+            &per_cu, reinterpret_cast<const void *>(&step_tab_kernel<P, TPW, G, BX, GS>), 64 * W, 0);
         if (e != hipSuccess) return e;
         e = hipGetDevice(&dev);
         if (e != hipSuccess) return e;
@@ -2298,21 +2227,18 @@ static hipError_t launch_tab_p(StepParams prm, const fe_mesh *m, hipStream_t s) 
         resident = std::max(1, per_cu) * std::max(1, cus);
         attr = true;
     }
-    prm.A = PREC == 0 ? (const void *)m->d_Af64s : (const void *)m->d_Af32s;
-    prm.S = CPX ? m->d_Sf64s : nullptr;
+    prm.A = m->d_Af32s;
     prm.zl = m->seg_zl;
     prm.nfz = (int)m->nf[2];
     const int ngroups = (prm.nchunk + G - 1) / G;
-    // the table of this brick shape (y bricks: the first table)
-    const std::vector<int64_t> &off = BY > 1 || m->seg_by == 1 ? m->seg_off : m->seg_off1;
-    const int32_t *tab0 = BY > 1 || m->seg_by == 1 ? m->d_segtab : m->d_segtab1;
+    const std::vector<int64_t> &off = m->seg_off;
     for (size_t col = 0; col + 1 < off.size(); ++col) {
         const int64_t segs = off[col + 1] - off[col];
         if (segs == 0) continue;
-        const int2 *tab = reinterpret_cast<const int2 *>(tab0) + off[col];
+        const int2 *tab = reinterpret_cast<const int2 *>(m->d_segtab) + off[col];
         const int64_t nitems = segs * ngroups;
         const int64_t grid = std::min<int64_t>(nitems, resident);
-        hipLaunchKernelGGL((step_tab_kernel<P, PREC, TPW, G, BX, BY, CPX, GS>), dim3((unsigned)grid), dim3(64 * W), 0, s, prm,
+        hipLaunchKernelGGL((step_tab_kernel<P, TPW, G, BX, GS>), dim3((unsigned)grid), dim3(64 * W), 0, s, prm,
                            tab, m->d_tabperm, nitems);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -2320,30 +2246,19 @@ static hipError_t launch_tab_p(StepParams prm, const fe_mesh *m, hipStream_t s) 
     return hipSuccess;
 }
 
-template <int P, int PREC, int BY, bool CPX>
-static hipError_t launch_tab_y(StepParams prm, const fe_mesh *m, hipStream_t s) {
-    typedef TabCfg<P, PREC> C;
+template <int P>
+static hipError_t launch_tab(StepParams prm, const fe_mesh *m, hipStream_t s) {
+    typedef TabCfg<P> C;
     switch (m->seg_bx) {
-    case 3: return launch_tab_p<P, PREC, C::TPW, C::G, 3, BY, CPX, C::GS>(prm, m, s);
-    case 2: return launch_tab_p<P, PREC, C::TPW, C::G, 2, BY, CPX, C::GS>(prm, m, s);
-    default: return launch_tab_p<P, PREC, C::TPW, C::G, 1, BY, CPX, C::GS>(prm, m, s);
+    case 3: return launch_tab_p<P, C::TPW, C::G, 3, C::GS>(prm, m, s);
+    case 2: return launch_tab_p<P, C::TPW, C::G, 2, C::GS>(prm, m, s);
+    default: return launch_tab_p<P, C::TPW, C::G, 1, C::GS>(prm, m, s);
     }
 }
 
-// FP64 products walk the bricks with y extent (2 cells where the mesh
-// allows): fewer bytes, and faster where the products dominate; FP32
-// products, HBM-bound, were measured faster on bricks one cell deep in y
-// (the second table), where a brick's cells are closer together in memory.
-template <int P, int PREC, bool CPX = false>
-static hipError_t launch_tab(StepParams prm, const fe_mesh *m, hipStream_t s) {
-    if constexpr (PREC == 0)
-        if (m->seg_by == 2) return launch_tab_y<P, PREC, 2, CPX>(prm, m, s);
-    return launch_tab_y<P, PREC, 1, CPX>(prm, m, s);
-}
-
-// Cells per brick along an axis of the table kernel (x: up to 3, y: up to
-// 2): the largest length that divides the axis' cell count and leaves a
-// periodic axis at least two bricks; 1 when there is none above 1.
+// Cells per brick along x of the table kernel: the largest length up to 3 that
+// divides the axis' cell count and leaves at least two bricks on a periodic
+// axis.
 static int brick_length(const fe_mesh *m, int axis, int most) {
     const int n = m->ncell[axis];
     for (int L = most; L >= 2; --L)
@@ -2356,9 +2271,8 @@ static int brick_length(const fe_mesh *m, int axis, int most) {
 // the rows a wave owns (its tiles wave + W j, 16 rows each) hold whole
 // classes of nodes linked by the holds: the two nodes of a cell at i = 0 and
 // i = p with the same (j, k) read and write the same x-face hold slot at one
-// position, those at j = 0, p with the same (i, k) the same back-face slot,
-// those at k = 0, p with the same (i, j) the same top-face slot.  The
-// classes (8 corners; 4 nodes of an edge; 2 of a face; 1 inside) are placed
+// position, those at k = 0, p with the same (i, j) the same top-face slot.  The
+// classes, closed under j = 0, p too (8 corners; 4 nodes of an edge; 2 of a face; 1 inside) are placed
 // largest first into the first wave with room (their sizes divide a wave's
 // rows, so they always fit).
 void build_table_row_perm(int p, int tiles_per_wave, std::vector<int32_t> &perm) {
@@ -2397,19 +2311,17 @@ void build_table_row_perm(int p, int tiles_per_wave, std::vector<int32_t> &perm)
 int table_tiles_per_wave(int p) { return p == 5 ? TabCfg<5>::TPW : TabCfg<4>::TPW; }
 
 // Segment table of the table kernel (host): for every colour pass, in launch
-// order, the bricks of that colour (BX cells along x by BY along y by zl
-// along z), in the order the kernel walks them, one entry each (see SEG_FM /
+// order, the bricks of that colour (BX cells along x by zl along z), in the order the kernel walks them, one entry each (see SEG_FM /
 // SEG_DM / SEG_WM; the bits describe the brick's outer faces).  Bricks are
 // coloured along each axis as cells are.
-void build_segment_table(const fe_mesh *m, int by_most, std::vector<int32_t> &tab, std::vector<int64_t> &off,
-                         int &zl_out, int &bx_out, int &by_out) {
+void build_segment_table(const fe_mesh *m, std::vector<int32_t> &tab, std::vector<int64_t> &off, int &zl_out,
+                         int &bx_out) {
     tab.clear();
     off.assign(1, 0);
     const int P = m->p;
-    const int zl = zseg_length(m), bxl = brick_length(m, 0, 3), byl = brick_length(m, 1, by_most);
+    const int zl = zseg_length(m), bxl = brick_length(m, 0, 3);
     zl_out = zl;
     bx_out = bxl;
-    by_out = byl;
     AxisInfo ax[3];
     for (int d = 0; d < 3; ++d) {
         ax[d].ncell = m->ncell[d];
@@ -2417,9 +2329,9 @@ void build_segment_table(const fe_mesh *m, int by_most, std::vector<int32_t> &ta
         ax[d].bc = m->bc[d];
         ax[d].ncol = m->ncol[d];
     }
-    // the brick axes: x in runs of bxl cells, y of byl, z of zl
+    // the brick axes: x in runs of bxl cells, z of zl
     AxisInfo bk[3] = {ax[0], ax[1], ax[2]};
-    const int len[3] = {bxl, byl, zl};
+    const int len[3] = {bxl, 1, zl};
     for (int a = 0; a < 3; ++a) {
         bk[a].ncell = ax[a].ncell / len[a];
         bk[a].ncol = (bk[a].bc == FE_BC_PERIODIC && (bk[a].ncell & 1)) ? 3 : bk[a].ncell >= 2 ? 2 : 1;
@@ -2456,7 +2368,7 @@ void build_segment_table(const fe_mesh *m, int by_most, std::vector<int32_t> &ta
                             for (int a = 0; a < 3; ++a)
                                 b[a] = col[a] == 2 ? bk[a].ncell - 1 : col[a] + 2 * ic[2 - a];
                             const int I0 = first_free(ax[0], b[0] * bxl) +
-                                           (int)m->nf[0] * (first_free(ax[1], b[1] * byl) +
+                                           (int)m->nf[0] * (first_free(ax[1], b[1]) +
                                                             (int)m->nf[1] * first_free(ax[2], b[2] * zl));
                             int fm = 0, dm = 0, wm = 0;
                             for (int a = 0; a < 3; ++a) {
@@ -2475,17 +2387,15 @@ void build_segment_table(const fe_mesh *m, int by_most, std::vector<int32_t> &ta
             }
 }
 
-// Whether the table kernel applies: FP64 (p = 3, 4) or FP32 (p = 3, 4, 5)
-// products, real mode, folded cell matrix and segment table (no Neumann
-// axis), one leading
+// Whether a block has the layout of the table kernel (FP32 products at p = 3, 4
+// and 5): folded cell matrix and segment table (no Neumann axis), one leading
 // dimension for X, Y and the previous iterate, 16-byte requests at every row
 // and column pair (blocks 16-byte aligned, even leading dimension), and X
-// request offsets within the 31-bit range of its buffer requests.
+// request offsets within the 31-bit range of its buffer requests.  Variant 10
+// keeps the same line in FP64 (p = 3, 4) for the tensor-product kernel.
 static bool dma_applies(const fe_mesh *m, const StepArgs &a, fe_dtype prec) {
     if (!m->d_segtab || m->p < 3 || m->p > 5 || (m->p == 5 && prec != FE_F32)) return false;
-    // the Bloch mode: FP64 at p = 3, 4, with the folded k.G fragments
-    if (a.S && (prec != FE_F64 || m->p > 4 || !m->d_Sf64s)) return false;
-    if (!(prec == FE_F64 ? m->d_Af64s != nullptr : prec == FE_F32 && m->d_Af32s != nullptr)) return false;
+    if (a.S || prec == FE_BF16) return false;
     const uintptr_t ptrs = reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(a.Y) |
                            reinterpret_cast<uintptr_t>(a.Ym1 ? a.Ym1 : a.X);
     const bool same_ld = a.ldy == a.ldx && (!a.Ym1 || a.ldm == a.ldx);
@@ -2548,10 +2458,10 @@ hipError_t launch_step(const fe_mesh *m, const StepArgs &a, fe_dtype prec, hipSt
 
 static hipError_t launch_step_v(const fe_mesh *m, const StepArgs &a, fe_dtype prec, hipStream_t s, int variant) {
     // the tensor-product kernel: the FP64 default wherever it applies (see
-    // tensor_default), and variant 10 in FP64 on the blocks the table kernel
-    // would take
-    if (prec == FE_F64 && !a.S && tensor_applies(m, a) &&
-        (variant == 0 ? tensor_default(m, a) : variant == 10 && a.N >= 32 && dma_applies(m, a, prec)))
+    // tensor_default), variant 10 in FP64 on the blocks the table kernel
+    // would take, and variants 0 and 10 in the Bloch mode
+    if (prec == FE_F64 && tensor_applies(m, a) &&
+        (variant == 0 ? tensor_default(m, a) : variant == 10 && (a.S || (a.N >= 32 && dma_applies(m, a, prec)))))
         return launch_tensor(m, a, s);
     StepParams prm;
     prm.X = a.X; prm.ldx = a.ldx;
@@ -2578,22 +2488,8 @@ static hipError_t launch_step_v(const fe_mesh *m, const StepArgs &a, fe_dtype pr
     prm.zl = 1;
     if (a.S) {
         if (prec != FE_F64) return hipErrorInvalidValue;
-        // Bloch mode: the table kernel with the k.G product (p = 3, 4) on the
-        // whole 32-column groups (16 complex vectors), the rest in the
-        // row-owner kernel
-        if ((variant == 0 || variant == 10) && a.N >= 32 && dma_applies(m, a, prec)) {
-            const int64_t Nf = a.N / 32 * 32;
-            prm.N = Nf;
-            prm.nchunk = (int)(Nf / 16);
-            const hipError_t e = m->p == 3 ? launch_tab<3, 0, true>(prm, m, s) : launch_tab<4, 0, true>(prm, m, s);
-            if (e != hipSuccess || Nf == a.N) return e;
-            StepArgs rest = a;
-            rest.X += Nf;
-            rest.Y += Nf;
-            if (rest.Ym1) rest.Ym1 += Nf;
-            rest.N = a.N - Nf;
-            return launch_step_v(m, rest, prec, s, 6);
-        }
+        // Bloch mode where the tensor-product kernel does not apply, and the
+        // other variants:
         // the FP64 row-owner kernel in the configurations of the real mode,
         // with one wave less per SIMD for the second fragment stream
         switch (m->p) {
@@ -2617,21 +2513,16 @@ static hipError_t launch_step_v(const fe_mesh *m, const StepArgs &a, fe_dtype pr
         default: break;
         }
     }
-    // variant 10: the table kernel with direct-to-LDS prefetch (bricks) on
-    // the whole 32-vector groups, FP64 (p = 3, 4) or FP32 (p = 3, 4, 5) cell
-    // products; the columns past the last whole group (fewer than 32) go to
-    // the z-segment pipelined kernel (the default wherever it applies, where
-    // it was measured fastest: FP64 4.48 against 5.75, FP32 3.26 against
-    // 4.17 ms per H~X for the z-segment kernel on the 24x24x48-cell p = 4
-    // slab, 256 vectors)
-    const bool tab = variant == 10 || (variant == 0 && (prec == FE_F64 || prec == FE_F32));
-    if (tab && a.N >= 32 && dma_applies(m, a, prec)) {
+    // FP32 products: the table kernel with direct-to-LDS prefetch (bricks) on
+    // the whole 32-vector groups; the columns past the last whole group (fewer
+    // than 32) go to the z-segment pipelined kernel (the default wherever it
+    // applies, where it was measured fastest: 3.26 against 4.17 ms per H~X for
+    // the z-segment kernel on the 24x24x48-cell p = 4 slab, 256 vectors)
+    if ((variant == 10 || variant == 0) && prec == FE_F32 && a.N >= 32 && dma_applies(m, a, prec)) {
         const int64_t Nf = a.N / 32 * 32;
         prm.N = Nf;
         prm.nchunk = (int)(Nf / 16);
-        hipError_t e = hipErrorInvalidValue;
-        if (prec == FE_F64) e = m->p == 3 ? launch_tab<3, 0>(prm, m, s) : launch_tab<4, 0>(prm, m, s);
-        else e = m->p == 3 ? launch_tab<3, 1>(prm, m, s) : m->p == 4 ? launch_tab<4, 1>(prm, m, s) : launch_tab<5, 1>(prm, m, s);
+        const hipError_t e = m->p == 3 ? launch_tab<3>(prm, m, s) : m->p == 4 ? launch_tab<4>(prm, m, s) : launch_tab<5>(prm, m, s);
         if (e != hipSuccess || Nf == a.N) return e;
         StepArgs rest = a;
         rest.X += Nf;
@@ -2641,7 +2532,7 @@ static hipError_t launch_step_v(const fe_mesh *m, const StepArgs &a, fe_dtype pr
         return launch_step_v(m, rest, prec, s, 9);
     }
     // the pipelined kernel walking z segments is the default at p = 4 for all
-    // three product precisions, where it was measured fastest (FP64 5.7-6.0
+    // three product precisions where the kernels above do not apply (FP64 5.7-6.0
     // against 5.9-6.1 for the one-cell pipelined kernel, FP32 4.24 against
     // 5.8, BF16 3.84 against 5.0 for the multi-chunk kernel, ms per H~X on
     // the 24x24x48-cell slab, 256 vectors)

@@ -146,8 +146,11 @@ void cell_matrix_half(int p, int rule, double h, std::vector<double> &A) {
 // The one-dimensional factors of the folded cell matrix: with d_i the M^-1/2
 // factor of local index i of a node inside the mesh (its GLL mass (h/2) w_i,
 // twice that at a cell face), Ma = d (h/2 Mhat) d and Ka = d (1/2 2/h Khat) d,
-// so that D^ (1/2 Kc) D^ = Ka (x) Ma (x) Ma + Ma (x) Ka (x) Ma + Ma (x) Ma (x) Ka.
-void axis_matrices(int p, int rule, double h, std::vector<double> &Ma, std::vector<double> &Ka) {
+// so that D^ (1/2 Kc) D^ = Ka (x) Ma (x) Ma + Ma (x) Ka (x) Ma + Ma (x) Ma (x) Ka;
+// and Ga = d Chat d with Chat_ij = int l_i l_j' (its h/2 and 2/h cancel), so that
+// D^ (k_x G_x + k_y G_y) D^ = k_x Ga (x) Ma (x) Ma + k_y Ma (x) Ga (x) Ma (x first).
+void axis_matrices(int p, int rule, double h, std::vector<double> &Ma, std::vector<double> &Ka,
+                   std::vector<double> &Ga) {
     std::vector<double> K, M, x, w;
     ref_matrices(p, rule, K, M);
     gll_rule(p, x, w);
@@ -156,10 +159,13 @@ void axis_matrices(int p, int rule, double h, std::vector<double> &Ma, std::vect
     for (int i = 0; i < n; ++i) d[i] = 1.0 / std::sqrt((i == 0 || i == p ? h : 0.5 * h) * w[i]);
     Ma.assign(n * n, 0.0);
     Ka.assign(n * n, 0.0);
+    Ga.assign(n * n, 0.0);
+    const std::vector<double> D = Barycentric(x).diff_matrix();
     for (int i = 0; i < n; ++i)
         for (int j = 0; j < n; ++j) {
             Ma[i * n + j] = d[i] * (0.5 * h * M[i * n + j]) * d[j];
             Ka[i * n + j] = d[i] * (K[i * n + j] / h) * d[j];
+            Ga[i * n + j] = d[i] * (w[i] * D[i * n + j]) * d[j];
         }
 }
 

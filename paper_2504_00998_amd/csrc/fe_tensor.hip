@@ -47,7 +47,9 @@
 // 2.47 (the table kernel 4.73) = 4.4 TB/s of the 24 bytes per value, of 5.9 that
 // two reads and a write stream at; p = 6, 16x16x32 cells, 128 vectors 1.56
 // (5.53); p = 5, 20x20x40 cells, 200 vectors 3.16 (8.79); p = 3, 24x24x48 cells,
-// 100 vectors 0.50 (1.45); p = 2, 30x30x60 cells, 100 vectors 0.29 (1.09).
+// 100 vectors 0.50 (1.45); p = 2, 30x30x60 cells, 100 vectors 0.29 (1.09); the
+// Bloch mode on the p = 4 slab with 128 complex vectors 2.53 (7.4, the table kernel
+// with dense k.G products).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -89,6 +91,32 @@ constexpr int sym_count(int p) {
     return n;
 }
 
+// Off-diagonal entries of the one-dimensional advection matrix above the
+// diagonal that differ: it is antisymmetric, and equal to itself reflected in
+// the other diagonal.  (Its diagonal is zero but for the ends, which cancel
+// between the two cells of a vertex.)
+constexpr int anti_key(int p, int i, int j) {
+    const int a = i * 16 + j, b = (p - j) * 16 + p - i;
+    return a < b ? a : b;
+}
+constexpr int anti_id(int p, int i, int j) {
+    const int key = anti_key(p, i, j);
+    int n = 0;
+    for (int a = 0; a <= p; ++a)
+        for (int b = a + 1; b <= p; ++b)
+            if (anti_key(p, a, b) == a * 16 + b) {
+                if (a * 16 + b == key) return n;
+                ++n;
+            }
+    return -1;
+}
+constexpr int anti_count(int p) {
+    int n = 0;
+    for (int a = 0; a <= p; ++a)
+        for (int b = a + 1; b <= p; ++b) n += anti_key(p, a, b) == a * 16 + b;
+    return n;
+}
+
 }  // namespace
 
 struct TensorAxis {
@@ -98,7 +126,7 @@ struct TensorAxis {
     int ncell;
 };
 
-template <int P> struct TensorParams {
+template <int P, bool CPX> struct TensorParams {
     const double *X, *Ym1, *v;
     double *Y;
     int64_t px, py, pm, pv;           // plane strides in bytes
@@ -109,6 +137,7 @@ template <int P> struct TensorParams {
     int gw;                           // column groups side by side in the order of the items
     TensorAxis ax[3];
     double M[sym_count(P)], K[sym_count(P)], M2, K2;  // M2, K2: the vertex entries of two cells
+    double GX[CPX ? anti_count(P) : 1], GY[CPX ? anti_count(P) : 1];  // k_x, k_y times the advection matrix
 };
 
 namespace {
@@ -165,6 +194,16 @@ __device__ __forceinline__ LdsDouble *lds_at(uint32_t bytes) {
     return (LdsDouble *)(uintptr_t)bytes;
 }
 
+// The value of the lane beside this one in its pair (the other half of a
+// complex vector).
+__device__ __forceinline__ double neighbour(double x) {
+    const u32x2 w = __builtin_bit_cast(u32x2, x);
+    u32x2 o;
+    o.x = (uint32_t)__builtin_amdgcn_mov_dpp((int)w.x, 0xB1, 0xF, 0xF, true);
+    o.y = (uint32_t)__builtin_amdgcn_mov_dpp((int)w.y, 0xB1, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, o);
+}
+
 // A sum that is formed by here (the compiler may not defer it).
 __device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
 
@@ -202,9 +241,14 @@ template <int P, int BX, int BY, int XC> struct TensorShape {
     static_assert(LDS * 8 <= 160 * 1024, "LDS of a workgroup");
 };
 
-template <int P, int BX, int BY, int XC, int OCC>
+// CPX: the Bloch-k mode, columns complex vectors as interleaved (re, im)
+// pairs.  The operator gains -i (k_x G (x) M (x) M + k_y M (x) G (x) M), and
+// -i g (x_r + i x_i) = g x_i - i g x_r: in the x stage, whose lanes hold pairs,
+// G_x u of the other half joins K_x u; in the y stage G_y M_x u of a lane's own
+// column goes to its neighbour.
+template <int P, int BX, int BY, int XC, int OCC, bool CPX>
 __global__ __launch_bounds__((TensorShape<P, BX, BY, XC>::T)) __attribute__((amdgpu_waves_per_eu(OCC)))
-void tensor_step_kernel(TensorParams<P> k) {
+void tensor_step_kernel(TensorParams<P, CPX> k) {
     typedef TensorShape<P, BX, BY, XC> S;
     constexpr int NV = S::NV, WX = S::WX, RY = S::RY, RS = S::RS, NX = (XC + 1) * P + 1;
     __shared__ __align__(16) double lds[S::LDS];
@@ -235,16 +279,21 @@ void tensor_step_kernel(TensorParams<P> k) {
     const bool live = col < k.N;
     const uint32_t cb = (uint32_t)col * 8u;
     // the entries of the one-dimensional matrices, in scalar registers for the
-    // walk up to p = 4; above they do not fit beside the planes' descriptors
+    // walk up to p = 4 (3 for complex vectors); above they do not fit beside the planes' descriptors
     // and are read again (from the scalar cache) in every plane
+    typedef TensorParams<P, CPX> Params;
     typedef const __attribute__((address_space(4))) double *Entries;
     Entries cf = (Entries)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
-                           offsetof(TensorParams<P>, M));
+                           offsetof(Params, M));
+    constexpr bool RELOAD = P >= 5 || (CPX && P == 4);
+    constexpr int NG = anti_count(P);
     constexpr int NS = sym_count(P);
 #define TM(i, j) cf[sym_id(P, (i), (j))]
 #define TK(i, j) cf[NS + sym_id(P, (i), (j))]
 #define TM2 cf[2 * NS]
 #define TK2 cf[2 * NS + 1]
+#define TGX(i, j) ((i) < (j) ? cf[2 * NS + 2 + anti_id(P, (i), (j))] : -cf[2 * NS + 2 + anti_id(P, (j), (i))])
+#define TGY(i, j) ((i) < (j) ? cf[2 * NS + 2 + NG + anti_id(P, (i), (j))] : -cf[2 * NS + 2 + NG + anti_id(P, (j), (i))])
 
     if (__builtin_amdgcn_readfirstlane(tid) >= 64 * S::CW) {
         // x waves: row xrow of the tile's input rows, cells xs XC .. + XC, vectors
@@ -294,7 +343,7 @@ void tensor_step_kernel(TensorParams<P> k) {
             }
         };
         auto stage = [&](const Pair (&x)[NX], int buf) {
-            if constexpr (P >= 5) opaque(cf);
+            if constexpr (RELOAD) opaque(cf);
             {
                 LdsDouble *const w = lds_at(vlds + 8 * sub);
 #pragma unroll
@@ -315,12 +364,24 @@ void tensor_step_kernel(TensorParams<P> k) {
                                 constexpr int j = decltype(JQ)::value;
                                 mm = __builtin_fma(TM(P, j), x[c * P + j][h], mm);
                                 qq = __builtin_fma(TK(P, j), x[c * P + j][h], qq);
+                                if constexpr (CPX) {
+                                    const double g = TGX(P, j);
+                                    qq = __builtin_fma(h ? -g : g, x[c * P + j][1 - h], qq);
+                                }
                             });
                         unroll<1, P + 1>([&](auto JQ) {
                             constexpr int j = decltype(JQ)::value;
                             mm = __builtin_fma(TM(i, j), x[(c + 1) * P + j][h], mm);
                             qq = __builtin_fma(TK(i, j), x[(c + 1) * P + j][h], qq);
                         });
+                        if constexpr (CPX)
+                            unroll<0, P + 1>([&](auto JQ) {
+                                constexpr int j = decltype(JQ)::value;
+                                if constexpr (i != j) {
+                                    const double g = TGX(i, j);
+                                    qq = __builtin_fma(h ? -g : g, x[(c + 1) * P + j][1 - h], qq);
+                                }
+                            });
                         m[h] = mm;
                         q[h] = qq;
                     }
@@ -379,6 +440,8 @@ void tensor_step_kernel(TensorParams<P> k) {
     const uint32_t in = lds0 + 8 * (min(yc, BY - 1) * P * RS + yx * NV + vec);
     const uint32_t din = lds0 + 8 * (2 * RY * RS + min(yc, BY - 1) * P * RS + yx * NV + vec);
 
+    const double sign = vec & 1 ? -1.0 : 1.0;  // of the other half's G u in a re and an im column
+
     // planes of the previous iterate in flight: two where the registers
     // allow and a layer's planes take the two sets in turn
     constexpr int DEPTH = P == 2 || P == 4 ? 2 : 1;
@@ -407,7 +470,7 @@ void tensor_step_kernel(TensorParams<P> k) {
     // of the layer that it closes are this workgroup's
     auto plane = [&](auto JJ, int g, bool flush) {
         constexpr int J = decltype(JJ)::value;
-        if constexpr (P >= 5) opaque(cf);
+        if constexpr (RELOAD) opaque(cf);
         lds_barrier();
         stage_end();
         const uint32_t buf = (g - g0) & 1 ? 8 * S::BUF : 0;
@@ -423,7 +486,7 @@ void tensor_step_kernel(TensorParams<P> k) {
         for (int r = 0; r < P; ++r) pin(acc[JO][r]);
         stage_end();
         issue(g + DEPTH, vm[J % DEPTH]);
-        double A[P], B[P];
+        double A[P], B[P], C[CPX ? P : 1];
         unroll<0, 2 * P + 1>([&](auto RR) {
             constexpr int r = decltype(RR)::value, j = r - P;
             // (bounds the LDS reads in flight)
@@ -441,8 +504,17 @@ void tensor_step_kernel(TensorParams<P> k) {
                     A[i] = __builtin_fma(mm, pr, A[i]);
                     B[i] = __builtin_fma(kk, pr, __builtin_fma(mm, qr, B[i]));
                 }
+                if constexpr (CPX) {
+                    if constexpr (r == (i == 0 ? 0 : P)) C[i] = (j < 0 ? TGY(P, r) : TGY(i, 0)) * pr;
+                    else if constexpr (j < 0) C[i] = __builtin_fma(TGY(P, r), pr, C[i]);
+                    else if constexpr (j != i) C[i] = __builtin_fma(TGY(i, j), pr, C[i]);
+                }
             });
         });
+        if constexpr (CPX) {
+#pragma unroll
+            for (int r = 0; r < P; ++r) B[r] = __builtin_fma(sign, neighbour(C[r]), B[r]);
+        }
         stage_end();
         // z stage
         if constexpr (J > 0) {
@@ -496,6 +568,8 @@ void tensor_step_kernel(TensorParams<P> k) {
 #undef TK
 #undef TM2
 #undef TK2
+#undef TGX
+#undef TGY
 }
 
 // Cell layers per workgroup along z: as many workgroups as keep the chip busy
@@ -516,14 +590,14 @@ static int layers_per_group(int64_t columns, int ncz, int p, int64_t slots) {
     return best;
 }
 
-template <int P, int BX, int BY, int XC, int OCC>
+template <int P, int BX, int BY, int XC, int OCC, bool CPX>
 static hipError_t launch_tensor_p(const fe_mesh *m, const StepArgs &a, hipStream_t s) {
     typedef TensorShape<P, BX, BY, XC> S;
     // workgroups the chip holds at once
     static const int resident = [] {
         int per_cu = 0, dev = 0, cus = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, reinterpret_cast<const void *>(&tensor_step_kernel<P, BX, BY, XC, OCC>), S::T, 0) != hipSuccess ||
+                &per_cu, reinterpret_cast<const void *>(&tensor_step_kernel<P, BX, BY, XC, OCC, CPX>), S::T, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
             (void)hipGetLastError();
@@ -531,7 +605,7 @@ static hipError_t launch_tensor_p(const fe_mesh *m, const StepArgs &a, hipStream
         }
         return std::max(1, per_cu) * std::max(1, cus);
     }();
-    TensorParams<P> k;
+    TensorParams<P, CPX> k;
     const int64_t plane = m->nf[0] * m->nf[1];
     k.X = a.X;
     k.Y = a.Y;
@@ -565,6 +639,12 @@ static hipError_t launch_tensor_p(const fe_mesh *m, const StepArgs &a, hipStream
             k.M[sym_id(P, i, j)] = m->axisM[(size_t)i * (P + 1) + j];
             k.K[sym_id(P, i, j)] = m->axisK[(size_t)i * (P + 1) + j];
         }
+    if constexpr (CPX)
+        for (int i = 0; i <= P; ++i)
+            for (int j = i + 1; j <= P; ++j) {
+                k.GX[anti_id(P, i, j)] = m->kvec[0] * m->axisG[(size_t)i * (P + 1) + j];
+                k.GY[anti_id(P, i, j)] = m->kvec[1] * m->axisG[(size_t)i * (P + 1) + j];
+            }
     k.M2 = 2.0 * m->axisM[0];
     k.K2 = 2.0 * m->axisK[0];
     k.ntx = (m->ncell[0] + BX - 1) / BX;
@@ -584,7 +664,7 @@ static hipError_t launch_tensor_p(const fe_mesh *m, const StepArgs &a, hipStream
     k.items = (int)items;
     k.per_xcd = (int)((items + 7) / 8);
     const unsigned blocks = (unsigned)(8 * k.per_xcd);
-    hipLaunchKernelGGL((tensor_step_kernel<P, BX, BY, XC, OCC>), dim3(blocks), dim3(S::T), 0, s, k);
+    hipLaunchKernelGGL((tensor_step_kernel<P, BX, BY, XC, OCC, CPX>), dim3(blocks), dim3(S::T), 0, s, k);
     return hipGetLastError();
 }
 
@@ -593,7 +673,7 @@ static hipError_t launch_tensor_p(const fe_mesh *m, const StepArgs &a, hipStream
 // cell), a plane of every block within the 31 bits of its buffer requests,
 // and a recurrence whose beta / alpha is a number.
 bool tensor_applies(const fe_mesh *m, const StepArgs &a) {
-    if (m->axisM.empty() || a.S) return false;
+    if (m->axisM.empty()) return false;
     const int64_t plane = m->nf[0] * m->nf[1], ld = std::max(std::max(a.ldx, a.ldy), a.Ym1 ? a.ldm : (int64_t)0);
     if (ld > (int64_t)0x7FFFFFFF / 8 / plane) return false;
     if (a.N >= (int64_t)1 << 31) return false;
@@ -606,8 +686,10 @@ bool tensor_applies(const fe_mesh *m, const StepArgs &a) {
 // up to a mesh of the size where Lanczos and CG spend time on the product,
 // are documented to equal the one-cell kernel (variant 1) bit for bit.  The
 // rule looks at the number of vectors, not of real columns, so that a complex
-// block at the Gamma point takes the kernel of its real and imaginary parts.
+// block at the Gamma point takes the kernel of its real and imaginary parts; at
+// other k-points (no such equality there) it has no line.
 bool tensor_default(const fe_mesh *m, const StepArgs &a) {
+    if (a.S) return true;
     const int64_t vectors = a.vectors ? a.vectors : a.N;
     if (vectors < 3) return false;
     return m->p == 3 || m->p == 4 || m->ncells >= 64;
@@ -622,16 +704,21 @@ bool tensor_default(const fe_mesh *m, const StepArgs &a) {
 // 0.53; p = 7 (1, 1) 0.60 / 0.66, (1, 2) 0.68 / 0.71.  Two waves on a cell's rows
 // (half the output planes each) were no faster at any degree.
 hipError_t launch_tensor(const fe_mesh *m, const StepArgs &a, hipStream_t s) {
+#define FE_TENSOR(PP, BX, BY, XC, OCC, CBX, CBY, CXC, COCC)                             \
+    case PP:                                                                            \
+        return a.S ? launch_tensor_p<PP, CBX, CBY, CXC, COCC, true>(m, a, s)            \
+                   : launch_tensor_p<PP, BX, BY, XC, OCC, false>(m, a, s);
     switch (m->p) {
-    case 1: return launch_tensor_p<1, 4, 8, 2, 4>(m, a, s);
-    case 2: return launch_tensor_p<2, 3, 6, 3, 4>(m, a, s);
-    case 3: return launch_tensor_p<3, 2, 6, 2, 3>(m, a, s);
-    case 4: return launch_tensor_p<4, 2, 4, 2, 3>(m, a, s);
-    case 5: return launch_tensor_p<5, 1, 4, 1, 3>(m, a, s);
-    case 6: return launch_tensor_p<6, 1, 2, 1, 2>(m, a, s);
-    case 7: return launch_tensor_p<7, 1, 1, 1, 2>(m, a, s);
+        FE_TENSOR(1, 4, 8, 2, 4, 4, 8, 2, 4)
+        FE_TENSOR(2, 3, 6, 3, 4, 3, 6, 3, 4)
+        FE_TENSOR(3, 2, 6, 2, 3, 2, 6, 2, 3)
+        FE_TENSOR(4, 2, 4, 2, 3, 2, 4, 2, 3)
+        FE_TENSOR(5, 1, 4, 1, 3, 1, 4, 1, 3)
+        FE_TENSOR(6, 1, 2, 1, 2, 1, 2, 1, 2)
+        FE_TENSOR(7, 1, 1, 1, 2, 1, 1, 1, 2)
     default: return hipErrorInvalidValue;
     }
+#undef FE_TENSOR
 }
 
 }  // namespace fe

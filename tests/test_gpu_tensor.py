@@ -73,3 +73,28 @@ def test_tensor_kernel_matches_oracle(p, cells, bc, N, pad):
         gm.hx(X, Y)
         part = gm.hx(X[:, 1:].contiguous())
         assert torch.equal(part, Y[:, 1:])
+
+
+@pytest.mark.parametrize("p,cells,N", [(1, (5, 9, 4), 3), (2, (4, 7, 5), 9), (3, (3, 2, 7), 8), (4, (5, 5, 3), 1),
+                                       (5, (2, 5, 3), 7), (6, (3, 3, 2), 2), (7, (2, 2, 3), 9)])
+def test_tensor_kernel_bloch_matches_oracle(p, cells, N):
+    """The k.G term of complex vectors at every degree (one, eight and a few
+    vectors past a group of eight; tiles with remainders along x and y)."""
+    import paper_2504_00998_amd as fe
+    wl = W.small_slab(cells, p=p, N=N, m=5)
+    print("case: tensor bloch", p, cells, N, flush=True)
+    om = O.Mesh.from_workload(wl)
+    Vq = W.workload_potential(wl, om.quad_points())
+    op = O.Operator(om, Vq, wl.E, wl.z0)
+    gm = fe.Mesh.from_workload(wl)
+    gm.set_potential(torch.from_numpy(Vq).cuda(), wl.E, wl.z0)
+    k = (0.37, -0.61)
+    gm.set_kpoint(*k)
+    B = O.BlochOperator(op, om, k)
+    Xh = wl.Xc(op.n)
+    X = torch.from_numpy(Xh).cuda()
+    Y = gm.hx_k(X)
+    assert torch.equal(gm.hx_k(X), Y)
+    for Yd, R, bar in ((Y, B.apply(Xh), 1e-13),
+                       (gm.cheb_filter_k(X, 5, 3.0, 900.0, -1.0), B.filter(Xh, 5, 3.0, 900.0, -1.0), 1e-12)):
+        assert (np.linalg.norm(Yd.cpu().numpy() - R, axis=0) / np.linalg.norm(R, axis=0)).max() < bar
