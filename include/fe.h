@@ -96,7 +96,8 @@ fe_status fe_mesh_destroy(fe_mesh *mesh);
  * which applies the stiffness axis by axis in one launch, for blocks of three
  * vectors or more on meshes without a zero-Neumann axis (p = 3 and 4; the
  * other degrees from 64 cells on), as long as one z plane of a block is below
- * 2 GiB; the kernels below elsewhere.  1 = one cell x 16 vectors per
+ * 2 GiB; its form for one or two vectors on meshes of 1024 cells and more, with
+ * any boundary conditions; the kernels below elsewhere.  1 = one cell x 16 vectors per
  * workgroup, cell matrix streamed from L2 (the plain reference form);
  * 3 / 4 = one cell x 32 / 64 vectors per workgroup, so each cell-matrix
  * fragment read from L2 feeds 2 / 4 products (falls back to 1 when the block

@@ -286,13 +286,29 @@ fe_status fe_mesh_create(const fe_mesh_desc *d, fe_mesh **out) {
         }
         m->maxf = std::max<int>(m->maxf, (int)m->nf[a]);
     }
-    std::vector<double> axis(9 * (size_t)m->maxf, 0.0);
-    for (int a = 0; a < 3; ++a)
+    std::vector<double> axis(15 * (size_t)m->maxf, 0.0), Khat, Mhat;
+    ref_matrices(m->p, m->rule, Khat, Mhat);
+    for (int a = 0; a < 3; ++a) {
+        // the assembled diagonals of the axis' reference stiffness and mass
+        const int64_t k = (int64_t)m->ncell[a] * m->p;
+        for (int c = 0; c < m->ncell[a]; ++c)
+            for (int i = 0; i <= m->p; ++i) {
+                int64_t g = (int64_t)c * m->p + i;
+                if (m->bc[a] == FE_BC_DIRICHLET) {
+                    if (g == 0 || g == k) continue;
+                    --g;
+                } else if (m->bc[a] == FE_BC_PERIODIC && g == k) {
+                    g = 0;
+                }
+                axis[(size_t)(9 + a) * m->maxf + g] += Khat[(size_t)i * (m->p + 1) + i];
+                axis[(size_t)(12 + a) * m->maxf + g] += Mhat[(size_t)i * (m->p + 1) + i];
+            }
         for (int64_t t = 0; t < m->nf[a]; ++t) {
             axis[(size_t)a * m->maxf + t] = 1.0 / std::sqrt(m->axis_mass[a][t]);
             axis[(size_t)(3 + a) * m->maxf + t] = 1.0 / m->axis_mass[a][t];
             axis[(size_t)(6 + a) * m->maxf + t] = m->axis_mass[a][t];
         }
+    }
     std::vector<double> wrel(3 * (size_t)m->n1);
     for (int a = 0; a < 3; ++a)
         for (int i = 0; i <= m->p; ++i) wrel[(size_t)a * m->n1 + i] = 0.5 * h * m->w[i];
@@ -312,10 +328,10 @@ fe_status fe_mesh_create(const fe_mesh_desc *d, fe_mesh **out) {
     const bool table = fold && m->p >= 3 && m->p <= 5 && m->n < INT32_MAX;
     std::vector<int32_t> perm;
     if (table) build_table_row_perm(m->p, table_tiles_per_wave(m->p), perm);
+    axis_matrices(m->p, m->rule, h, m->axisM, m->axisK, m->axisG);
     std::vector<double> f64s;
     std::vector<float> f32s;
     if (fold) {
-        axis_matrices(m->p, m->rule, h, m->axisM, m->axisK, m->axisG);
         fold_swizzle(m, m->cellA, table ? &perm : nullptr, f64s);
         f32s.assign(f64s.begin(), f64s.end());
     }

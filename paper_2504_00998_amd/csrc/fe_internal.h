@@ -71,7 +71,7 @@ struct fe_mesh {
     std::vector<double> axis_coord[3];  // coordinate of each free node position
     std::vector<double> axis_mass[3];   // assembled 1-D lumped mass per free position
 
-    // with no Neumann axis: the one-dimensional cell matrices of one axis,
+    // the one-dimensional cell matrices of one axis,
     // (p + 1)^2 row-major, scaled by the per-local-index M^-1/2 of a node
     // inside the mesh: axisM the mass, axisK the stiffness times 1/2, so that
     // D^ (1/2 Kc) D^ is the sum of the three products of one axisK and two
@@ -79,8 +79,9 @@ struct fe_mesh {
     std::vector<double> axisM, axisK, axisG;
 
     // device
-    // [9][maxf]: per axis a, rows a / 3 + a / 6 + a hold M^-1/2, M^-1 and M of
-    // the assembled 1-D lumped mass at each free position
+    // [15][maxf]: per axis a, rows a / 3 + a / 6 + a hold M^-1/2, M^-1 and M of
+    // the assembled 1-D lumped mass at each free position, rows 9 + a / 12 + a the
+    // assembled diagonals of the reference stiffness and mass
     double *d_axis = nullptr;
     double *d_zcoord = nullptr;   // [nf_z] z coordinate of free z positions
     int maxf = 0;
@@ -152,10 +153,10 @@ struct StepArgs {
 bool tensor_applies(const fe_mesh *m, const StepArgs &a);
 bool tensor_default(const fe_mesh *m, const StepArgs &a);
 hipError_t launch_tensor(const fe_mesh *m, const StepArgs &a, hipStream_t s);
+bool tensor_vec_applies(const fe_mesh *m, const StepArgs &a);
+hipError_t launch_tensor_vec(const fe_mesh *m, const StepArgs &a, hipStream_t s, const double *done = nullptr,
+                             double *part = nullptr, int max_parts = 0, int *nparts = nullptr);
 hipError_t launch_step(const fe_mesh *m, const StepArgs &a, fe_dtype prec, hipStream_t s);
-// single-vector FP64 product in two launches (cell products, then nodal sums)
-size_t assembled_scratch_doubles(const fe_mesh *m);
-hipError_t launch_step_assembled(const fe_mesh *m, const StepArgs &a, double *Zc, hipStream_t s);
 hipError_t launch_potential(const fe_mesh *m, const double *Vq, double E, double z0, hipStream_t s);
 hipError_t launch_potential_vjp(const fe_mesh *m, const double *g, double z0, double *Vbar, double *Ebar,
                                 hipStream_t s);

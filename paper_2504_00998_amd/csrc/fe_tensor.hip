@@ -122,7 +122,7 @@ constexpr int anti_count(int p) {
 struct TensorAxis {
     int K;     // ncell * p: the period, or the last node of a Dirichlet axis
     int nfree;
-    int per;   // -1: periodic, 0: Dirichlet
+    int per;   // -1: periodic, 0: Dirichlet, 1 (single vectors only): zero-Neumann
     int ncell;
 };
 
@@ -673,7 +673,8 @@ static hipError_t launch_tensor_p(const fe_mesh *m, const StepArgs &a, hipStream
 // cell), a plane of every block within the 31 bits of its buffer requests,
 // and a recurrence whose beta / alpha is a number.
 bool tensor_applies(const fe_mesh *m, const StepArgs &a) {
-    if (m->axisM.empty()) return false;
+    for (int d = 0; d < 3; ++d)
+        if (m->bc[d] == FE_BC_NEUMANN) return false;
     const int64_t plane = m->nf[0] * m->nf[1], ld = std::max(std::max(a.ldx, a.ldy), a.Ym1 ? a.ldm : (int64_t)0);
     if (ld > (int64_t)0x7FFFFFFF / 8 / plane) return false;
     if (a.N >= (int64_t)1 << 31) return false;
@@ -719,6 +720,396 @@ hipError_t launch_tensor(const fe_mesh *m, const StepArgs &a, hipStream_t s) {
     default: return hipErrorInvalidValue;
     }
 #undef FE_TENSOR
+}
+
+// ------------------------------------------------------------ single vectors
+// The same step for one column (Lanczos, conjugate gradients): the lanes run
+// over the nodes.  A workgroup owns BX x BY cells and a range of layers, its
+// planes of X go through LDS (coalesced along x, one plane ahead in registers),
+// the x stage takes a cell of a row a lane, the y-z stages an x position of a
+// cell a lane; two barriers a plane.  Bound by the chain of a plane (about
+// 1.7 us: LDS, barrier, x stage, LDS, barrier, y and z stages): a vector of
+// 1.8 M nodes is in the caches, and the ranges along z are as short as one layer
+// so that the chip is filled, at the price of the layer below each being walked
+// again.  us per product, cell products with a second launch that adds them up
+// or the coloured cell kernel / this one: p = 4 24x24x48 cells 97 / 23.4, p = 3
+// 80 / 13.3.  From 24x24x6 to x24 cells 17-18 us, 48x48x96 96 us.  Tiles of 4x4
+// to 16x4 cells and 2 or 4 planes of X ahead took 24.5-30 us at p = 4.
+//
+// NEU: some axis is zero-Neumann.  The even extension over such a face
+// satisfies the same equations with whole vertex masses, in which the face
+// node's scaled value is sqrt(2) times as large and its result 1/sqrt(2): X is
+// reflected and multiplied when it is loaded, the sums when they are stored.
+// DOT: the bare product H0 x (no diagonal term or previous iterate, alpha 1), and
+// part[workgroup] = sum over its outputs of x times y; a layer's own x waits in
+// LDS for the layer to close.
+template <int P, int BX, int BY> struct TensorVecShape {
+    static constexpr int WX = BX * P, RX = (BX + 1) * P + 1, RY = (BY + 1) * P + 1;
+    static constexpr int YI = WX * BY, XI = RY * BX;       // y-z and x items
+    static constexpr int T = ((YI > XI ? YI : XI) + 63) / 64 * 64;
+    static constexpr int XR = (XI + T - 1) / T, LR = (RX * RY + T - 1) / T;
+    static constexpr int XS = RX | 1, LW = WX | 1;         // odd row strides in LDS
+    static constexpr int LDS = RY * XS + 2 * RY * LW;
+    static_assert(T <= 1024, "threads of a workgroup");
+};
+
+template <int P> struct TensorVecParams {
+    const double *X, *Ym1, *v;
+    double *Y;
+    int64_t px, py, pm, pv;
+    uint32_t rx, ry, rm, rv, ldx, ldy, ldm;
+    double alpha, nba, shift;
+    int ntx, nty, nzc, layers, last;  // last: closing layer along z (the cell count, or one more on a Neumann axis)
+    TensorAxis ax[3];
+    const double *done;               // DOT: nonzero, nothing to do
+    double *part;
+    double M[sym_count(P)], K[sym_count(P)], M2, K2;
+};
+
+namespace {
+
+constexpr int kNeumann = 1;  // TensorAxis.per of a zero-Neumann axis
+
+// free_node with zero-Neumann axes (the even extension over their faces)
+template <bool NEU> __device__ __forceinline__ int free_node_n(const TensorAxis &a, int g) {
+    if constexpr (NEU) {
+        if (a.per == kNeumann) {
+            int f = g < 0 ? -g : g;
+            f = f > a.K ? 2 * a.K - f : f;
+            return f < 0 ? -1 : f;
+        }
+    }
+    return free_node(a, g);
+}
+// whether node g (of the axis itself) is on a zero-Neumann face
+template <bool NEU> __device__ __forceinline__ bool on_neumann_face(const TensorAxis &a, int g) {
+    return NEU && a.per == kNeumann && (g == 0 || g == a.K);
+}
+// whether node g of cell c is one of the axis' outputs
+template <bool NEU> __device__ __forceinline__ bool axis_output(const TensorAxis &a, int c, int g) {
+    if (NEU && a.per == kNeumann) return g <= a.K;
+    return c < a.ncell && free_node(a, g) >= 0;
+}
+
+}  // namespace
+
+template <int P, int BX, int BY, bool NEU, bool DOT>
+__global__ __launch_bounds__((TensorVecShape<P, BX, BY>::T))
+void tensor_vec_kernel(TensorVecParams<P> k) {
+    typedef TensorVecShape<P, BX, BY> S;
+    constexpr int T = S::T, WX = S::WX, RX = S::RX, RY = S::RY, XS = S::XS, LW = S::LW, LR = S::LR;
+    __shared__ double lds[S::LDS + (DOT ? P * P * T : 0)];
+    double *const lx = lds, *const lp = lds + RY * XS, *const lq = lp + RY * LW;
+    if constexpr (DOT) {
+        if (*k.done != 0.0) return;  // whole grid
+    }
+    int rest = (int)blockIdx.x;
+    const int tx = rest % k.ntx;
+    rest /= k.ntx;
+    const int ty = rest % k.nty, zc = rest / k.nty;
+    const int cx0 = tx * BX, cy0 = ty * BY, cz0 = zc * k.layers, cz1 = min(cz0 + k.layers, k.last);
+    const int l0 = k.ax[2].per != 0 || cz0 > 0 ? cz0 - 1 : cz0, g1 = cz1 * P;
+    const uint32_t cb = blockIdx.y * 8u;  // the column
+    const int tid = threadIdx.x;
+    constexpr double R2 = 1.4142135623730951, H2 = 0.70710678118654757;
+
+    // loads: element tid + T q of the tile's RX x RY nodes
+    uint32_t off[LR];
+    double in_scale[NEU ? LR : 1];
+#pragma unroll
+    for (int q = 0; q < LR; ++q) {
+        const int idx = tid + T * q, row = idx / RX, cx = idx % RX;
+        const int gx = cx0 * P - P + cx, gy = cy0 * P - P + row;
+        const int fx = free_node_n<NEU>(k.ax[0], gx), fy = free_node_n<NEU>(k.ax[1], gy);
+        off[q] = idx < RX * RY && fx >= 0 && fy >= 0 ? (uint32_t)(fy * k.ax[0].nfree + fx) * k.ldx + cb : kAbsent;
+        if constexpr (NEU)
+            in_scale[q] = (on_neumann_face<NEU>(k.ax[0], gx) ? R2 : 1.0) * (on_neumann_face<NEU>(k.ax[1], gy) ? R2 : 1.0);
+    }
+    // y-z item: x position yx, cell yc
+    const int yx = tid % WX, yc = min(tid / WX, BY - 1);
+    uint32_t oy[2], om[2], ov[2];
+    double out_scale[NEU ? 2 : 1], inv_scale[NEU ? 2 : 1];
+    {
+        const int gx = cx0 * P + yx;
+        const bool in = tid < S::YI && axis_output<NEU>(k.ax[0], cx0 + yx / P, gx);
+        const int fx = free_node_n<NEU>(k.ax[0], gx);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int gy = (cy0 + yc) * P + r, fy = free_node_n<NEU>(k.ax[1], gy);
+            const bool ok = in && r < P && axis_output<NEU>(k.ax[1], cy0 + yc, gy);
+            const uint32_t row = (uint32_t)(fy * k.ax[0].nfree + fx);
+            oy[r] = ok ? row * k.ldy + cb : kAbsent;
+            om[r] = ok ? row * k.ldm + cb : kAbsent;
+            ov[r] = ok ? row * 8u : kAbsent;
+            if constexpr (NEU) {
+                const bool ex = on_neumann_face<NEU>(k.ax[0], gx), ey = on_neumann_face<NEU>(k.ax[1], gy);
+                out_scale[r] = (ex ? H2 : 1.0) * (ey ? H2 : 1.0);
+                inv_scale[r] = (ex ? R2 : 1.0) * (ey ? R2 : 1.0);
+            }
+        }
+    }
+#define TM(i, j) k.M[sym_id(P, (i), (j))]
+#define TK(i, j) k.K[sym_id(P, (i), (j))]
+    double acc[P + 1][P], xr[LR], vm[DOT ? 1 : P], vv[DOT ? 1 : P], dot = 0.0;
+    double *const lk = lds + S::LDS + tid;
+#pragma unroll
+    for (int i = 0; i <= P; ++i)
+#pragma unroll
+        for (int r = 0; r < P; ++r) acc[i][r] = 0.0;
+    auto outside = [&](int g) { return ((g - cz0 * P) >> 31) | ((g1 - 1 - g) >> 31) | ((k.ax[2].K - g) >> 31); };
+    auto issue_x = [&](int g) {
+        const __amdgpu_buffer_rsrc_t r = plane_of(k.X, k.px, k.rx, free_node_n<NEU>(k.ax[2], g) | ((g1 - g) >> 31));
+#pragma unroll
+        for (int q = 0; q < LR; ++q) {
+            const uint32_t o = off[q];
+            xr[q] = buf_load(r, o, 0);
+        }
+    };
+    auto issue_base = [&](int g) {
+        if constexpr (DOT) return;
+        const int f = free_node_n<NEU>(k.ax[2], g) | outside(g);
+        const __amdgpu_buffer_rsrc_t bm = plane_of(k.Ym1, k.pm, k.rm, f), bv = plane_of(k.v, k.pv, k.rv, f);
+        const uint32_t sm = (uint32_t)k.ax[0].nfree * k.ldm, sv = (uint32_t)k.ax[0].nfree * 8u;
+#pragma unroll
+        for (int r = 0; r < P; ++r) {
+            const uint32_t a = om[r ? 1 : 0], b = ov[r ? 1 : 0], q = r ? r - 1 : 0;
+            vm[r] = buf_load(bm, a, q * sm);
+            vv[r] = buf_load(bv, b, q * sv);
+        }
+    };
+    auto plane = [&](auto JJ, int g, bool flush) {
+        constexpr int J = decltype(JJ)::value;
+        const double zin = NEU && on_neumann_face<NEU>(k.ax[2], g) ? R2 : 1.0;
+#pragma unroll
+        for (int q = 0; q < LR; ++q) {
+            const int idx = tid + T * q, row = idx / RX, cx = idx % RX;
+            if (idx < RX * RY) lx[row * XS + cx] = NEU ? xr[q] * (in_scale[q] * zin) : xr[q];
+        }
+        lds_barrier();
+        issue_x(g + 1);
+#pragma unroll
+        for (int q = 0; q < S::XR; ++q) {
+            const int it = tid + T * q, row = it % RY, c = it / RY;
+            if (it < S::XI) {
+                const double *x = lx + row * XS + c * P;
+                double *o = lp + row * LW + c * P;
+                double u[2 * P + 1];
+#pragma unroll
+                for (int j = 0; j <= 2 * P; ++j) u[j] = x[j];
+                unroll<0, P>([&](auto II) {
+                    constexpr int i = decltype(II)::value;
+                    double m = (i == 0 ? k.M2 : TM(i, 0)) * u[P], t = (i == 0 ? k.K2 : TK(i, 0)) * u[P];
+                    if constexpr (i == 0)
+                        unroll<0, P>([&](auto JQ) {
+                            constexpr int j = decltype(JQ)::value;
+                            m = __builtin_fma(TM(P, j), u[j], m);
+                            t = __builtin_fma(TK(P, j), u[j], t);
+                        });
+                    unroll<1, P + 1>([&](auto JQ) {
+                        constexpr int j = decltype(JQ)::value;
+                        m = __builtin_fma(TM(i, j), u[P + j], m);
+                        t = __builtin_fma(TK(i, j), u[P + j], t);
+                    });
+                    o[i] = m;
+                    o[RY * LW + i] = t;
+                });
+            }
+        }
+        constexpr int JO = J == 0 ? P : J;
+        const double *const own = lx + (P + yc * P) * XS + P + yx;
+        double bx[DOT ? P : 1];
+#pragma unroll
+        for (int r = 0; r < P; ++r) {
+            if constexpr (DOT) {
+                bx[r] = own[r * XS];
+            } else {
+                double pm = vm[r];
+                if constexpr (NEU) pm *= inv_scale[r ? 1 : 0] * zin;
+                acc[JO][r] = __builtin_fma(k.nba, pm, __builtin_fma(vv[r] - k.shift, own[r * XS], acc[JO][r]));
+            }
+        }
+        issue_base(g + 1);
+        lds_barrier();
+        double A[P], B[P];
+        unroll<0, 2 * P + 1>([&](auto RR) {
+            constexpr int r = decltype(RR)::value, j = r - P;
+            const double pr = lp[(yc * P + r) * LW + yx], qr = lq[(yc * P + r) * LW + yx];
+            unroll<0, (j < 0 ? 1 : P)>([&](auto II) {
+                constexpr int i = decltype(II)::value;
+                const double mm = j < 0 ? TM(P, r) : j == 0 && i == 0 ? k.M2 : TM(i, j < 0 ? 0 : j);
+                const double kk = j < 0 ? TK(P, r) : j == 0 && i == 0 ? k.K2 : TK(i, j < 0 ? 0 : j);
+                if constexpr (r == (i == 0 ? 0 : P)) {
+                    A[i] = mm * pr;
+                    B[i] = __builtin_fma(mm, qr, kk * pr);
+                } else {
+                    A[i] = __builtin_fma(mm, pr, A[i]);
+                    B[i] = __builtin_fma(kk, pr, __builtin_fma(mm, qr, B[i]));
+                }
+            });
+        });
+        if constexpr (J > 0) {
+            unroll<0, P + 1>([&](auto II) {
+                constexpr int i = decltype(II)::value;
+#pragma unroll
+                for (int r = 0; r < P; ++r)
+                    acc[i][r] = __builtin_fma(TK(i, J), A[r], __builtin_fma(TM(i, J), B[r], acc[i][r]));
+            });
+        } else {
+            unroll<0, P + 1>([&](auto II) {
+                constexpr int i = decltype(II)::value;
+                if constexpr (i < P) {
+                    const int go = g - P + i;
+                    const int f = free_node_n<NEU>(k.ax[2], go) | (flush ? outside(go) : -1);
+                    const __amdgpu_buffer_rsrc_t by = plane_of(k.Y, k.py, k.ry, f);
+                    const uint32_t sy = (uint32_t)k.ax[0].nfree * k.ldy;
+                    const double zs = NEU && on_neumann_face<NEU>(k.ax[2], go) ? H2 : 1.0;
+#pragma unroll
+                    for (int r = 0; r < P; ++r) {
+                        double t = __builtin_fma(TK(i, P), A[r], __builtin_fma(TM(i, P), B[r], acc[i][r]));
+                        const uint32_t o = oy[r ? 1 : 0], q = r ? r - 1 : 0;
+                        if constexpr (NEU) t *= out_scale[r ? 1 : 0] * zs;
+                        const double y = DOT ? t : k.alpha * t;
+                        buf_store(y, by, o, q * sy);
+                        if constexpr (DOT) {
+                            double x = lk[(i * P + r) * T];
+                            if constexpr (NEU) x *= out_scale[r ? 1 : 0] * zs;
+                            dot += o != kAbsent && f >= 0 ? x * y : 0.0;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < P; ++r)
+                    acc[i][r] = i == 0 ? __builtin_fma(k.K2, A[r], __builtin_fma(k.M2, B[r], acc[P][r]))
+                                       : __builtin_fma(TK(i, 0), A[r], TM(i, 0) * B[r]);
+            });
+        }
+        if constexpr (DOT) {
+#pragma unroll
+            for (int r = 0; r < P; ++r) lk[(J * P + r) * T] = bx[r];
+        }
+#pragma unroll
+        for (int i = 0; i <= P; ++i)
+#pragma unroll
+            for (int r = 0; r < P; ++r) pin(acc[i][r]);
+    };
+    issue_x(l0 * P);
+    issue_base(l0 * P);
+    for (int l = l0;; ++l) {
+        plane(std::integral_constant<int, 0>{}, l * P, l > cz0);
+        if (l == cz1) break;
+        unroll<1, P>([&](auto JJ) { plane(JJ, l * P + decltype(JJ)::value, false); });
+    }
+    if constexpr (DOT) {
+        // fixed-order sum over the workgroup
+        __syncthreads();
+        lds[tid] = dot;
+        __syncthreads();
+        for (int w = 512; w > 0; w >>= 1) {
+            if (tid < w && tid + w < T) lds[tid] += lds[tid + w];
+            __syncthreads();
+        }
+        if (tid == 0) k.part[blockIdx.x] = lds[0];
+    }
+#undef TM
+#undef TK
+}
+
+template <int P, int BX, int BY, bool NEU, bool DOT>
+static hipError_t launch_vec_p(const fe_mesh *m, const StepArgs &a, hipStream_t s, const double *done, double *part,
+                               int max_parts, int *nparts) {
+    typedef TensorVecShape<P, BX, BY> S;
+    static const int resident = [] {
+        int per_cu = 0, dev = 0, cus = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &per_cu, reinterpret_cast<const void *>(&tensor_vec_kernel<P, BX, BY, NEU, DOT>), S::T, 0) != hipSuccess ||
+            hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+            (void)hipGetLastError();
+            return 256;
+        }
+        return std::max(1, per_cu) * std::max(1, cus);
+    }();
+    TensorVecParams<P> k;
+    const int64_t plane = m->nf[0] * m->nf[1], ldm = a.Ym1 ? a.ldm : a.ldx;
+    k.X = a.X;
+    k.Y = a.Y;
+    k.Ym1 = a.Ym1 ? a.Ym1 : a.X;
+    k.v = a.v ? a.v : m->d_v;
+    k.ldx = (uint32_t)(a.ldx * 8);
+    k.ldy = (uint32_t)(a.ldy * 8);
+    k.ldm = (uint32_t)(ldm * 8);
+    k.px = plane * a.ldx * 8;
+    k.py = plane * a.ldy * 8;
+    k.pm = plane * ldm * 8;
+    k.pv = plane * 8;
+    k.rx = (uint32_t)(((plane - 1) * a.ldx + a.N) * 8);
+    k.ry = (uint32_t)(((plane - 1) * a.ldy + a.N) * 8);
+    k.rm = a.Ym1 ? (uint32_t)(((plane - 1) * ldm + a.N) * 8) : 0u;
+    k.rv = (uint32_t)k.pv;
+    k.alpha = a.alpha;
+    k.nba = a.Ym1 ? -a.beta / a.alpha : 0.0;
+    k.shift = a.shift;
+    int cells[3];  // with the one past a Neumann axis' last, whose only output is the face
+    for (int d = 0; d < 3; ++d) {
+        k.ax[d].K = m->ncell[d] * m->p;
+        k.ax[d].nfree = (int)m->nf[d];
+        k.ax[d].per = m->bc[d] == FE_BC_PERIODIC ? -1 : m->bc[d] == FE_BC_NEUMANN ? kNeumann : 0;
+        k.ax[d].ncell = m->ncell[d];
+        cells[d] = m->ncell[d] + (m->bc[d] == FE_BC_NEUMANN ? 1 : 0);
+    }
+    for (int i = 0; i <= P; ++i)
+        for (int j = 0; j <= P; ++j) {
+            k.M[sym_id(P, i, j)] = m->axisM[(size_t)i * (P + 1) + j];
+            k.K[sym_id(P, i, j)] = m->axisK[(size_t)i * (P + 1) + j];
+        }
+    k.M2 = 2.0 * m->axisM[0];
+    k.K2 = 2.0 * m->axisK[0];
+    k.ntx = (cells[0] + BX - 1) / BX;
+    k.nty = (cells[1] + BY - 1) / BY;
+    k.last = cells[2];
+    k.layers = layers_per_group((int64_t)k.ntx * k.nty * a.N, k.last, P, resident);
+    // (with partial sums: longer ranges where there would be too many)
+    while (DOT && k.layers < k.last && (int64_t)k.ntx * k.nty * ((k.last + k.layers - 1) / k.layers) > max_parts) ++k.layers;
+    k.nzc = (k.last + k.layers - 1) / k.layers;
+    const int64_t blocks = (int64_t)k.ntx * k.nty * k.nzc;
+    if (blocks > (1 << 30) || (DOT && blocks > max_parts)) return hipErrorInvalidValue;
+    k.done = done;
+    k.part = part;
+    if (nparts) *nparts = (int)blocks;
+    hipLaunchKernelGGL((tensor_vec_kernel<P, BX, BY, NEU, DOT>), dim3((unsigned)blocks, (unsigned)a.N), dim3(S::T), 0, s, k);
+    return hipGetLastError();
+}
+
+// One or two columns.  part (not null): also the partial sums of x times y over
+// the workgroups, *nparts of them (at most max_parts), unless *done is nonzero.
+bool tensor_vec_applies(const fe_mesh *m, const StepArgs &a) {
+    if (a.S || a.N < 1 || a.N > 2) return false;
+    const int64_t plane = m->nf[0] * m->nf[1], ld = std::max(std::max(a.ldx, a.ldy), a.Ym1 ? a.ldm : (int64_t)0);
+    if (ld > (int64_t)0x7FFFFFFF / 8 / plane) return false;
+    return a.alpha != 0.0 && std::isfinite(a.beta / a.alpha);
+}
+
+hipError_t launch_tensor_vec(const fe_mesh *m, const StepArgs &a, hipStream_t s, const double *done, double *part,
+                             int max_parts, int *nparts) {
+    const bool neu = m->bc[0] == FE_BC_NEUMANN || m->bc[1] == FE_BC_NEUMANN || m->bc[2] == FE_BC_NEUMANN;
+#define FE_VEC(PP, BX, BY)                                                                                        \
+    case PP:                                                                                                      \
+        if (part)                                                                                                 \
+            return neu ? launch_vec_p<PP, BX, BY, true, true>(m, a, s, done, part, max_parts, nparts)             \
+                       : launch_vec_p<PP, BX, BY, false, true>(m, a, s, done, part, max_parts, nparts);           \
+        return neu ? launch_vec_p<PP, BX, BY, true, false>(m, a, s, nullptr, nullptr, 0, nullptr)                 \
+                   : launch_vec_p<PP, BX, BY, false, false>(m, a, s, nullptr, nullptr, 0, nullptr);
+    switch (m->p) {
+        FE_VEC(1, 32, 8)
+        FE_VEC(2, 16, 8)
+        FE_VEC(3, 8, 8)
+        FE_VEC(4, 8, 8)
+        FE_VEC(5, 4, 8)
+        FE_VEC(6, 4, 8)
+        FE_VEC(7, 4, 8)
+    default: return hipErrorInvalidValue;
+    }
+#undef FE_VEC
 }
 
 }  // namespace fe

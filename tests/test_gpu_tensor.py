@@ -98,3 +98,41 @@ def test_tensor_kernel_bloch_matches_oracle(p, cells, N):
     for Yd, R, bar in ((Y, B.apply(Xh), 1e-13),
                        (gm.cheb_filter_k(X, 5, 3.0, 900.0, -1.0), B.filter(Xh, 5, 3.0, 900.0, -1.0), 1e-12)):
         assert (np.linalg.norm(Yd.cpu().numpy() - R, axis=0) / np.linalg.norm(R, axis=0)).max() < bar
+
+
+N_ = W.NEUMANN
+
+
+@pytest.mark.parametrize("p,cells,bc,N,pad", [
+    (1, (33, 9, 4), (P, P, D), 1, 0), (1, (8, 8, 16), (N_, D, N_), 2, 1),
+    (2, (17, 7, 9), (D, P, N_), 1, 2), (3, (9, 8, 15), (P, N_, P), 2, 0),
+    (4, (8, 8, 16), (D, D, D), 1, 0), (4, (9, 7, 17), (P, P, N_), 1, 1), (4, (2, 16, 32), (P, P, P), 2, 0),
+    (5, (5, 13, 16), (P, D, D), 1, 0), (6, (4, 9, 29), (N_, P, N_), 1, 0), (7, (5, 9, 23), (P, P, D), 2, 3)])
+def test_single_vector_kernel_matches_oracle(p, cells, bc, N, pad):
+    """One and two columns on meshes of 1024 cells and more: tiles with
+    remainders, a mesh of two cells along x, and zero-Neumann faces (reflected)
+    on each axis, for the bare product and with the previous iterate."""
+    import paper_2504_00998_amd as fe
+    wl = W.small_slab(cells, p=p, N=N, m=4, bc=bc, **({"E": 0.0} if bc[2] == P else {}))
+    print("case: single vector", p, cells, bc, N, pad, flush=True)
+    om = O.Mesh.from_workload(wl)
+    Vq = W.workload_potential(wl, om.quad_points())
+    op = O.Operator(om, Vq, wl.E, wl.z0)
+    gm = fe.Mesh.from_workload(wl)
+    gm.set_potential(torch.from_numpy(Vq).cuda(), wl.E, wl.z0)
+    Xh = wl.X(op.n)
+    buf = torch.full((op.n, N + pad), float("nan"), dtype=torch.float64, device="cuda")
+    buf[:, :N] = torch.from_numpy(Xh).cuda()
+    out = torch.full_like(buf, float("nan"))
+    X, Y = buf[:, :N], out[:, :N]
+
+    def err(Yd, R):
+        return (np.linalg.norm(Yd.cpu().numpy() - R, axis=0) / np.linalg.norm(R, axis=0)).max()
+
+    assert err(gm.hx(X, Y), op.apply(Xh)) < 1e-13
+    first = Y.clone()
+    assert torch.equal(gm.hx(X, Y), first)
+    if N == 2:
+        assert torch.equal(gm.hx(X[:, 1:].contiguous()), Y[:, 1:])
+    assert err(gm.cheb_filter(X, 4, 3.0, 900.0, -1.0, Y=Y), op.filter(Xh, 4, 3.0, 900.0, -1.0)) < 1e-12
+    assert torch.isnan(out[:, N:]).all()
