@@ -2,8 +2,8 @@
 //
 // Forward:  Y_1 = alpha_0 (H~ - c) Y_0,  Y_{k+1} = alpha_k (H~ - c) Y_k - beta_k Y_{k-1}.
 // For a cotangent G = dL/dY_m the adjoint runs k = m-1 .. 0:
-//   Ybar_k     += alpha_k (H~ - c) Ybar_{k+1}     (H~ symmetric: the same kernel),
-//   Ybar_{k-1}  = -beta_k Ybar_{k+1}               (its first contribution),
+//   Ybar_k  = alpha_k (H~ - c) Ybar_{k+1} - beta_{k+1} Ybar_{k+2}   (H~ symmetric:
+//             the same kernel; Ybar_{m+1} = 0),
 //   g_I        += alpha_k sum_j Ybar_{k+1}[I,j] Y_k[I,j],
 // where g = dL/dv is the derivative with respect to the diagonal potential
 // term v of H~ (the only place V_quad and E enter H~; paper Sec. 2.1 V_eff
@@ -168,13 +168,23 @@ fe_status fe_cheb_filter_vjp(fe_mesh *m, const double *X, const double *G, int64
                 const double *B1 = k + 1 == mdeg ? Gc : adj_buf(k + 1);
                 int64_t ld1 = k + 1 == mdeg ? ld : ldb;
                 double *Bk = adj_buf(k);
-                // Ybar_k += alpha_k (H~ - c) Ybar_{k+1}  (first contribution when k = m-1)
-                bool first = k == mdeg - 1;
-                rc = filter_step(m, B1, ld1, Bk, ldb, first ? nullptr : Bk, ldb, al[k], first ? 0.0 : -1.0, c, Nc,
-                                 prec, st);
+                // Ybar_k = alpha_k (H~ - c) Ybar_{k+1} - beta_{k+1} Ybar_{k+2}: the
+                // filter's own step on the last two adjoint blocks.  A pass that
+                // leaves -beta_{k+1} Ybar_{k+2} in Ybar_k first costs two more
+                // streams of n N values beside the step's three
+                const bool first = k == mdeg - 1;
+                const double *B2 = first ? nullptr : k + 2 == mdeg ? Gc : adj_buf(k + 2);
+                int64_t ld2 = k + 2 == mdeg ? ld : ldb;
+                double b2 = first ? 0.0 : be[k + 1];
+                if (prec != FE_F64 && k + 2 == mdeg) {
+                    // (the kernels with rounded products want one leading dimension)
+                    FE_HIPA(launch_axpby(Bk, ldb, Gc, ld, n, Nc, -b2, 0.0, st), "axpby");
+                    B2 = Bk;
+                    ld2 = ldb;
+                    b2 = -1.0;
+                }
+                rc = filter_step(m, B1, ld1, Bk, ldb, B2, ld2, al[k], b2, c, Nc, prec, st);
                 if (rc != FE_OK) return rc;
-                if (k >= 1)
-                    FE_HIPA(launch_axpby(adj_buf(k - 1), ldb, B1, ld1, n, Nc, -be[k], 0.0, st), "axpby");
                 int64_t ldk;
                 const double *Yk = Y_of(k, ldk);
                 FE_HIPA(launch_rowdot_accum(m, B1, ld1, Yk, ldk, Nc, al[k], g, st), "rowdot");

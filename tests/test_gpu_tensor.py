@@ -136,3 +136,34 @@ def test_single_vector_kernel_matches_oracle(p, cells, bc, N, pad):
         assert torch.equal(gm.hx(X[:, 1:].contiguous()), Y[:, 1:])
     assert err(gm.cheb_filter(X, 4, 3.0, 900.0, -1.0, Y=Y), op.filter(Xh, 4, 3.0, 900.0, -1.0)) < 1e-12
     assert torch.isnan(out[:, N:]).all()
+
+
+@pytest.mark.parametrize("prec,m,stride,pad", [("f64", 2, 1, 0), ("f64", 3, 2, 3), ("f32", 2, 1, 3), ("f32", 4, 2, 0)])
+def test_adjoint_step_takes_the_block_before_last(prec, m, stride, pad):
+    """The reverse sweep's three-block rotation where the cotangent itself is
+    one of the blocks (m = 2 and past it), over checkpoint segments and rows
+    wider than the block, in FP64 and with FP32 products (whose second step
+    takes a copy).  FP32: sums of 64 rounded products (64 eps = 4e-6) over up
+    to four steps."""
+    import paper_2504_00998_amd as fe
+    wl = W.small_slab((4, 3, 3), p=3, N=33, m=m)
+    print("case: adjoint", prec, m, stride, pad, flush=True)
+    om = O.Mesh.from_workload(wl)
+    Vq = W.workload_potential(wl, om.quad_points())
+    op = O.Operator(om, Vq, wl.E, wl.z0)
+    gm = fe.Mesh.from_workload(wl)
+    gm.set_potential(torch.from_numpy(Vq).cuda(), wl.E, wl.z0)
+    Xh = wl.X(op.n)
+    Gh = np.random.default_rng(3).standard_normal(Xh.shape)
+    a0, b, _ = O.lanczos_bounds(op.apply, wl.lanczos_start(op.n), 10)
+    a = O.weyl_cut(a0, b, wl.N, op.n)
+    wide = torch.zeros((2, op.n, wl.N + pad), dtype=torch.float64, device="cuda")
+    X, G = wide[0, :, :wl.N], wide[1, :, :wl.N]
+    X.copy_(torch.from_numpy(Xh))
+    G.copy_(torch.from_numpy(Gh))
+    Xb, Vb, _ = gm.cheb_filter_vjp(X, G, m, a, b, a0, prec=prec, ckpt_stride=stride)
+    R, g = op.filter_vjp(Xh, Gh, m, a, b, a0)
+    bar = 1e-12 if prec == "f64" else 2e-5
+    assert (np.linalg.norm(Xb.cpu().numpy() - R, axis=0) / np.linalg.norm(R, axis=0)).max() < bar
+    Rv = op.potential_vjp(g)[0]
+    assert np.abs(Vb.cpu().numpy() - Rv).max() / np.abs(Rv).max() < 10 * bar
