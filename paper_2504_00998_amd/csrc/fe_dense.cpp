@@ -162,14 +162,15 @@ extern "C" {
 
 fe_status fe_lanczos_bounds(fe_mesh *m, const double *v0, int32_t k, double *a0, double *b, hipStream_t s) {
     if (!m || !v0 || !a0 || !b) return fail(FE_EINVAL, "NULL argument");
-    if (k < 1 || k > 64) return fail(FE_EINVAL, "k must be in 1..64");
+    if (k < 1 || k > kLanczosMost) return fail(FE_EINVAL, "k must be in 1..64");
     if (!m->potential_set) return fail(FE_ESTATE, "fe_set_potential has not been called");
     int64_t n = m->n;
-    // scratch: V [n x (k+1)] column-major, w [n], h [k+1]
-    size_t need = ((size_t)n * (k + 2) + (k + 1) + 1024) * sizeof(double);
+    // scratch: V [n x k] column-major, w [n], alpha and beta [k each], partial sums
+    const size_t sums = (size_t)(kLanczosMost + 1) * kLanczosBlocks;
+    size_t need = ((size_t)n * (k + 1) + 2 * k + sums + 1024) * sizeof(double);
     fe_status st = ensure_scratch_dense(m, need);
     if (st != FE_OK) return st;
-    double *V = m->d_scratch + 1024, *w = V + (size_t)n * (k + 1), *hv = w + n;
+    double *V = m->d_scratch + 1024, *w = V + (size_t)n * k, *ab = w + n, *part = ab + 2 * k;
     rocblas_handle h;
     if ((st = handle(m, s, h)) != FE_OK) return st;
     int ni = (int)n;
@@ -180,27 +181,19 @@ fe_status fe_lanczos_bounds(fe_mesh *m, const double *v0, int32_t k, double *a0,
     double inv = 1.0 / nrm;
     FE_BLAS(rocblas_dscal(h, ni, &inv, V, 1), "dscal");
     std::vector<double> alpha(k), beta(k);
-    int kk = k;
     for (int j = 0; j < k; ++j) {
         double *vj = V + (size_t)j * n;
         StepArgs a{vj, 1, w, 1, nullptr, 0, 1.0, 0.0, 0.0, 1};
         FE_HIPD(launch_step(m, a, FE_F64, s), "step kernel launch");
         if (m->nl.n_site > 0) FE_HIPD(launch_nonlocal(m, vj, 1, w, 1, 1, 1.0, s), "nonlocal");
-        FE_BLAS(rocblas_ddot(h, ni, vj, 1, w, 1, &alpha[j]), "ddot");
-        // full reorthogonalisation, twice: w -= V (V^T w)
-        for (int pass = 0; pass < 2; ++pass) {
-            double one = 1.0, zero = 0.0, mone = -1.0;
-            FE_BLAS(rocblas_dgemv(h, rocblas_operation_transpose, ni, j + 1, &one, V, ni, w, 1, &zero, hv, 1), "dgemv T");
-            FE_BLAS(rocblas_dgemv(h, rocblas_operation_none, ni, j + 1, &mone, V, ni, hv, 1, &one, w, 1), "dgemv N");
-        }
-        FE_BLAS(rocblas_dnrm2(h, ni, w, 1, &beta[j]), "dnrm2");
-        if (beta[j] == 0.0) { kk = j + 1; break; }
-        if (j + 1 < k) {
-            double ib = 1.0 / beta[j];
-            FE_HIPD(hipMemcpyAsync(V + (size_t)(j + 1) * n, w, n * sizeof(double), hipMemcpyDeviceToDevice, s), "copy");
-            FE_BLAS(rocblas_dscal(h, ni, &ib, V + (size_t)(j + 1) * n, 1), "dscal");
-        }
+        // alpha_j = v_j . w; full reorthogonalisation, twice: w -= V (V^T w); beta_j
+        FE_HIPD(launch_lanczos(V, w, n, j + 1, j + 1 < k ? vj + n : nullptr, part, ab + j, ab + k + j, s), "lanczos");
     }
+    FE_HIPD(hipMemcpyAsync(alpha.data(), ab, k * sizeof(double), hipMemcpyDeviceToHost, s), "copy alpha");
+    FE_HIPD(hipMemcpyAsync(beta.data(), ab + k, k * sizeof(double), hipMemcpyDeviceToHost, s), "copy beta");
+    FE_HIPD(hipStreamSynchronize(s), "sync");
+    int kk = 1;  // up to an invariant subspace: what follows a zero beta is not used
+    while (kk < k && beta[kk - 1] != 0.0) ++kk;
     std::vector<double> T((size_t)kk * kk, 0.0), ev;
     for (int i = 0; i < kk; ++i) {
         T[i * kk + i] = alpha[i];

@@ -168,6 +168,9 @@ fe_status filter_step(fe_mesh *m, const double *X, int64_t ldx, double *Y, int64
 void cheb_coefficients(int mdeg, double a, double b, double a0, std::vector<double> &al, std::vector<double> &be,
                        double &c);
 fe_status validate_filter_args(fe_mesh *m, int64_t N, int32_t mdeg, double a, double b, double a0, fe_dtype prec);
+constexpr int kLanczosMost = 64, kLanczosBlocks = 512;  // columns; workgroups of its sums
+hipError_t launch_lanczos(const double *V, double *w, int64_t n, int nc, double *v, double *part, double *alpha,
+                          double *beta, hipStream_t s);
 hipError_t launch_fill(double *p, int64_t n, double v, hipStream_t s);
 fe_status ensure_scratch_dense(fe_mesh *m, size_t bytes);
 fe_status blas_handle(fe_mesh *m, hipStream_t s, void **h);

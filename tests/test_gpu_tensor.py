@@ -167,3 +167,25 @@ def test_adjoint_step_takes_the_block_before_last(prec, m, stride, pad):
     assert (np.linalg.norm(Xb.cpu().numpy() - R, axis=0) / np.linalg.norm(R, axis=0)).max() < bar
     Rv = op.potential_vjp(g)[0]
     assert np.abs(Vb.cpu().numpy() - Rv).max() / np.abs(Rv).max() < 10 * bar
+
+
+@pytest.mark.parametrize("p,cells,k", [(1, (3, 3, 3), 1), (2, (3, 4, 5), 8), (3, (4, 4, 3), 9), (4, (9, 9, 13), 17),
+                                       (3, (4, 4, 8), 64)])
+def test_lanczos_bounds_match_oracle(p, cells, k):
+    """One column to 64 (whole and broken groups of eight, one workgroup and
+    many) of the reorthogonalisation; the bounds' error is held against the
+    norm of H~: k steps of products and sums each good to about 1e-14."""
+    import paper_2504_00998_amd as fe
+    wl = W.small_slab(cells, p=p, N=2, m=4)
+    print("case: lanczos", p, cells, k, flush=True)
+    om = O.Mesh.from_workload(wl)
+    Vq = W.workload_potential(wl, om.quad_points())
+    op = O.Operator(om, Vq, wl.E, wl.z0)
+    gm = fe.Mesh.from_workload(wl)
+    gm.set_potential(torch.from_numpy(Vq).cuda(), wl.E, wl.z0)
+    v0 = wl.lanczos_start(op.n)
+    a0, b, _ = O.lanczos_bounds(op.apply, v0, k)
+    v = torch.from_numpy(v0).cuda()
+    got = gm.lanczos_bounds(v, k)
+    assert abs(got[0] - a0) < 1e-11 * b and abs(got[1] - b) < 1e-11 * b
+    assert gm.lanczos_bounds(v, k) == got
