@@ -34,19 +34,20 @@ PEAK = {"f64": (78.6, "mfma"), "f32": (157.3, "mfma"), "bf16": (2500.0, "mfma")}
 # measured on an MI355X with a register-only loop (FP64: 4x4x4 blocks, FP32:
 # 16x16x4); see paper_2504_00998_amd/microbench/mfma_rate.hip
 MEASURED_PEAK = {"f64": 74.2, "f32": 155.0}
-# HBM bytes per colour launch of the default step kernel on the p=4 slab
-# (N=256), from FETCH_SIZE/WRITE_SIZE counters scaled by a plain copy of known
-# size, averaged over the launches of a degree-30 filter (the first step reads
-# no previous iterate: FP64 1.467e9 B, FP32 1.588e9 B, BF16 1.779e9 B; the 29
-# others 1.950e9 / 2.065e9 / 2.235e9 B); valid for these kernel builds only
-# (None: not counted)
-COUNTED_TRAFFIC = {("slab-p4-24x24x48", 256, "f64"): (1.934e9, "step_tab_kernel<4,0,1,2,3,2>"),
-                   ("slab-p4-24x24x48", 256, "f32"): (2.049e9, "step_tab_kernel<4,1,1,2,3,1,false,2>"),
+# HBM bytes per launch of the default step kernel on the p=4 slab (N=256), from
+# FETCH_SIZE/WRITE_SIZE counters scaled by a plain copy of known size, averaged
+# over the launches of a degree-30 filter (the first step reads no previous
+# iterate).  FP64: the tensor-product kernel, one launch a step; FP32 and BF16
+# products: one of eight colour launches (FP32 1.588e9 B in the first step, BF16
+# 1.779e9 B; the 29 others 2.065e9 / 2.235e9 B); valid for these kernel builds
+# only (None: not counted)
+COUNTED_TRAFFIC = {("slab-p4-24x24x48", 256, "f64"): (1.194e10, "tensor_step_kernel<4,2,4,2,3,false>"),
+                   ("slab-p4-24x24x48", 256, "f32"): (2.049e9, "step_tab_kernel<4,1,2,3,2>"),
                    ("slab-p4-24x24x48", 256, "bf16"): (2.220e9, "step_pipe_kernel<4,2,2,true>")}
-# MI355X ceilings of the filter rate (GDoF.vec/s) of the large workloads:
-# the dense-MFMA roofline of one H~X (2 n_c^2 flop per cell and vector; FP64
-# 78.6, FP32 157.3 TFLOP/s) expressed per DoF and vector
-CEILING = {("slab-p6-16x16x32", "f64"): 71.8, ("slab-p5-40x40x80-nonlocal", "f32"): 210.0}
+# MI355X ceilings of the filter rate (GDoF.vec/s) of the large workloads: FP64,
+# the 24 B that a DoF and vector move at 8 TB/s; FP32, the dense-MFMA roofline of
+# one H~X (2 n_c^2 flop per cell and vector at 157.3 TFLOP/s)
+CEILING = {("slab-p6-16x16x32", "f64"): 333.3, ("slab-p5-40x40x80-nonlocal", "f32"): 210.0}
 GOLDEN_RITZ = os.path.join(ROOT, "tests", "golden", "cfg3_ritz_oracle.txt")
 
 
@@ -235,8 +236,11 @@ def large_workloads(dev, steps):
         nc = (wl.p + 1) ** 3
         flops_hx = 2.0 * nc * nc * wl.n_cells * N
         extra = {}
-        if prec != "f64":
-            # the same H~X with FP64 cell products (the row-owner kernel at p = 5)
+        if prec == "f64":  # tensor-product kernel: the dense product's flop are not done
+            extra = {"hx_TFLOPs": None, "hx_frac_of_mfma_peak": None,
+                     "hx_GBps_algorithmic": round(16.0 * n * N / (ms_hx * 1e-3) / 1e9, 1)}
+        else:
+            # the same H~X in FP64 (the tensor-product kernel)
             gm.hx(X, Y=Y, prec="f64")
             torch.cuda.synchronize()
             e0.record(stream)
@@ -244,9 +248,7 @@ def large_workloads(dev, steps):
             e1.record(stream)
             torch.cuda.synchronize()
             ms64 = e0.elapsed_time(e1)
-            extra = {"ms_per_hx_f64": round(ms64, 3),
-                     "hx_f64_TFLOPs": round(flops_hx / (ms64 * 1e-3) / 1e12, 3),
-                     "hx_f64_frac_of_mfma_peak": round(flops_hx / (ms64 * 1e-3) / 1e12 / PEAK["f64"][0], 4)}
+            extra = {"ms_per_hx_f64": round(ms64, 3)}
         value = m * n * N / (ms_f * 1e-3) / 1e9
         ceil = CEILING[(wl.name, prec)]
         out[wl.name] = {"prec": prec, "n_dof": n, "N": N, "m": m, "p": wl.p, "cells": list(wl.ncell),
@@ -336,7 +338,10 @@ def main():
     if not torch.isfinite(Y).all():
         raise RuntimeError("non-finite filter output")
 
-    # dominant kernel: one colour pass of the fused step kernel (8 colours per step)
+    # dominant kernel.  FP64 (variants 0 and 10): the tensor-product kernel, one
+    # launch a step, held against HBM; else one colour pass of the fused step
+    # kernel (8 colours per step), held against the MFMA rate of its dense product
+    tensor = args.prec == "f64" and args.variant in (0, 10)
     ncol = 1
     for a_ in range(3):
         nce, bc = wl.ncell[a_], wl.bc[a_]
@@ -345,7 +350,7 @@ def main():
     nc = (wl.p + 1) ** 3
     cells = wl.n_cells
     flops_per_launch = 2.0 * nc * nc * (cells / ncol) * N
-    launch_ms = (ms - t_pot) / launches
+    launch_ms = (ms - t_pot) / (m if tensor else launches)
     achieved = flops_per_launch / (launch_ms * 1e-3) / 1e12
     peak, bound = PEAK[args.prec]
     # the counters belong to the default kernel
@@ -381,20 +386,21 @@ def main():
                    "n_dof": n, "N": N, "m": m, "p": wl.p, "cells": list(wl.ncell), "prec": args.prec,
                    "kernel_variant": args.variant},
         "roofline": {
-            "bound": bound,
-            "achieved": round(achieved, 3),
-            "peak": peak,
-            "unit": "TFLOP/s",
-            "frac": round(achieved / peak, 4),
+            **({"bound": "hbm", "achieved": round(24.0 * n * N / (launch_ms * 1e-3) / 1e9, 1), "peak": 8000.0,
+                "unit": "GB/s", "frac": round(24.0 * n * N / (launch_ms * 1e-3) / 8e12, 4)} if tensor else
+               {"bound": bound, "achieved": round(achieved, 3), "peak": peak, "unit": "TFLOP/s",
+                "frac": round(achieved / peak, 4)}),
             "traffic": traffic[0] if traffic and traffic[0] else None,
             "traffic_unit": "B per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
-            "algorithmic_bytes_per_launch": 24.0 * n * N / ncol,
-            "kernel": (traffic[1] if traffic else f"step kernel p={wl.p} {args.prec}") + " (one colour pass)",
-            "measured_peak": MEASURED_PEAK.get(args.prec),
-            "frac_of_measured_peak": round(achieved / MEASURED_PEAK[args.prec], 4) if args.prec in MEASURED_PEAK else None,
-            "flops_per_launch": flops_per_launch,
+            "algorithmic_bytes_per_launch": 24.0 * n * N / (1 if tensor else ncol),
+            "kernel": (traffic[1] if traffic else f"step kernel p={wl.p} {args.prec}") + (
+                " (one Chebyshev step)" if tensor else " (one colour pass)"),
+            "measured_peak": None if tensor else MEASURED_PEAK.get(args.prec),
+            "frac_of_measured_peak": round(achieved / MEASURED_PEAK[args.prec], 4)
+            if args.prec in MEASURED_PEAK and not tensor else None,
+            "flops_per_launch": None if tensor else flops_per_launch,
             "avg_launch_ms": round(launch_ms, 5),
-            "launches_per_step": launches,
+            "launches_per_step": m if tensor else launches,
             "hbm_GBps": round(traffic[0] / (launch_ms * 1e-3) / 1e9, 1) if traffic and traffic[0] else None,
             "hbm_frac_of_8TBps": round(traffic[0] / (launch_ms * 1e-3) / 8e12, 4) if traffic and traffic[0] else None,
             "copy_GBps_measured": round(copy_GBps, 1),
@@ -436,7 +442,7 @@ def main():
     rec["poisson"] = {"n_dof": em.n, "bc": "periodic x,y / zero-Neumann z (zero-mean)", "tol": 1e-10,
                       "iterations": p_it, "relres": p_rel, "s": round(p_s, 4),
                       "ms_per_iteration": round(1e3 * p_s / max(p_it, 1), 4),
-                      "solver": "Jacobi-preconditioned CG on the device; product = all cell products, then fixed-order nodal sums; batches of 8 iterations replayed from a HIP graph"}
+                      "solver": "Jacobi-preconditioned CG on the device; three launches an iteration (single-vector tensor-product kernel with p.q, update, direction); batches of 8 iterations replayed from a HIP graph"}
     # Bloch form (Sec. 2.1): the same filter with complex H~^k at an in-plane
     # wave vector, on the same storage read as N/2 complex vectors
     # (interleaved re/im), FP64 only
@@ -459,17 +465,13 @@ def main():
         if not torch.isfinite(Y).all():
             raise RuntimeError("non-finite Bloch filter output")
         Nc = N // 2
-        # per colour launch: (1/2)K_c and k.G_c products on 2 Nc real columns
-        fl_k = 2.0 * 2.0 * nc * nc * (cells / ncol) * (2 * Nc)
-        lk_ms = ms_k / launches
+        lk_ms = ms_k / m
         rec["bloch"] = {"k": list(kb), "complex_vectors": Nc, "ms_per_filter": round(ms_k, 4),
                         "GDoF_cvec_per_s": round(m * n * Nc / (ms_k * 1e-3) / 1e9, 3),
-                        "avg_launch_ms": round(lk_ms, 5), "flops_per_launch": fl_k,
-                        "achieved_TFLOPs": round(fl_k / (lk_ms * 1e-3) / 1e12, 3),
-                        "frac_of_fp64_peak": round(fl_k / (lk_ms * 1e-3) / 1e12 / PEAK["f64"][0], 4),
-                        "kernel": (f"step_tab_kernel<{wl.p},0,...,CPX> (complex H~^k, the table kernel with the k.G "
-                                   "product, one colour pass)" if wl.p in (3, 4) else
-                                   f"step_row_kernel<{wl.p},0,...,CPX> (complex H~^k, one colour pass)")}
+                        "avg_launch_ms": round(lk_ms, 5),
+                        "GBps_algorithmic": round(24.0 * n * 2 * Nc / (lk_ms * 1e-3) / 1e9, 1),
+                        "kernel": "tensor_step_kernel<...,CPX> (complex H~^k, the k.G term beside the stiffness, one "
+                                  "launch a step)"}
     if not args.no_mixed and args.prec == "f64":
         t_pot_ms = t_pot
         rec["mixed_precision"] = mixed_precision_report(gm, wl, X, Y, work, a, b, a0, args.steps, ms - t_pot_ms,

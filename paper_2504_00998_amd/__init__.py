@@ -182,8 +182,8 @@ class Mesh:
 
     def set_kernel(self, variant: int):
         """Step-kernel implementation (``fe_mesh_set_kernel``): 0 = fastest
-        measured (default), 1 = one cell x 16 vectors per workgroup, 2-9 =
-        the alternatives declared in ``include/fe.h``."""
+        measured (default; in FP64 the tensor-product kernel), 1 = one cell x
+        16 vectors per workgroup, the others as declared in ``include/fe.h``."""
         _check(lib().fe_mesh_set_kernel(self._h, int(variant)))
 
     # ------------------------------------------------------------- geometry
