@@ -770,20 +770,33 @@ namespace {
 
 constexpr int kNeumann = 1;  // TensorAxis.per of a zero-Neumann axis
 
-// free_node with zero-Neumann axes (the even extension over their faces)
+// node of a zero-Neumann axis that node g of the even extension over its faces
+// is (negative where it is none)
+__device__ __forceinline__ int neumann_fold(const TensorAxis &a, int g) {
+    const int f = g < 0 ? -g : g;
+    return f > a.K ? 2 * a.K - f : f;
+}
+// free_node with zero-Neumann axes
 template <bool NEU> __device__ __forceinline__ int free_node_n(const TensorAxis &a, int g) {
     if constexpr (NEU) {
         if (a.per == kNeumann) {
-            int f = g < 0 ? -g : g;
-            f = f > a.K ? 2 * a.K - f : f;
+            const int f = neumann_fold(a, g);
             return f < 0 ? -1 : f;
         }
     }
     return free_node(a, g);
 }
-// whether node g (of the axis itself) is on a zero-Neumann face
+// whether node g of the extension is on a zero-Neumann face (on an axis of one
+// cell the reflected nodes -K and 2 K are too: each face is the other's
+// neighbour on both sides)
 template <bool NEU> __device__ __forceinline__ bool on_neumann_face(const TensorAxis &a, int g) {
-    return NEU && a.per == kNeumann && (g == 0 || g == a.K);
+    if constexpr (NEU) {
+        if (a.per == kNeumann) {
+            const int f = neumann_fold(a, g);
+            return f == 0 || f == a.K;
+        }
+    }
+    return false;
 }
 // whether node g of cell c is one of the axis' outputs
 template <bool NEU> __device__ __forceinline__ bool axis_output(const TensorAxis &a, int c, int g) {

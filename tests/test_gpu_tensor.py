@@ -189,3 +189,51 @@ def test_lanczos_bounds_match_oracle(p, cells, k):
     got = gm.lanczos_bounds(v, k)
     assert abs(got[0] - a0) < 1e-11 * b and abs(got[1] - b) < 1e-11 * b
     assert gm.lanczos_bounds(v, k) == got
+
+
+@pytest.mark.parametrize("p,cells,bc,N", [(2, (1, 32, 33), (N_, P, D), 1), (3, (33, 1, 32), (P, N_, N_), 2),
+                                          (4, (32, 33, 1), (P, P, N_), 1), (1, (1, 1, 1030), (N_, N_, D), 1)])
+def test_single_vector_kernel_on_a_neumann_axis_of_one_cell(p, cells, bc, N):
+    """One cell along a zero-Neumann axis: the nodes that the extension reaches
+    past either face are the other face's, which carries the face factor too."""
+    import paper_2504_00998_amd as fe
+    wl = W.small_slab(cells, p=p, N=N, m=4, bc=bc)
+    print("case: one Neumann cell", p, cells, bc, N, flush=True)
+    om = O.Mesh.from_workload(wl)
+    Vq = W.workload_potential(wl, om.quad_points())
+    op = O.Operator(om, Vq, wl.E, wl.z0)
+    gm = fe.Mesh.from_workload(wl)
+    gm.set_potential(torch.from_numpy(Vq).cuda(), wl.E, wl.z0)
+    Xh = wl.X(op.n)
+    X = torch.from_numpy(Xh).cuda()
+
+    def err(Yd, R):
+        return (np.linalg.norm(Yd.cpu().numpy() - R, axis=0) / np.linalg.norm(R, axis=0)).max()
+
+    assert err(gm.hx(X), op.apply(Xh)) < 1e-13
+    assert err(gm.cheb_filter(X, 4, 3.0, 900.0, -1.0), op.filter(Xh, 4, 3.0, 900.0, -1.0)) < 1e-12
+    v0 = wl.lanczos_start(op.n)
+    a0, b, _ = O.lanczos_bounds(op.apply, v0, 8)
+    got = gm.lanczos_bounds(torch.from_numpy(v0).cuda(), 8)
+    assert abs(got[0] - a0) < 1e-11 * b and abs(got[1] - b) < 1e-11 * b
+
+
+@pytest.mark.parametrize("p,cells,bc", [(2, (1, 4, 3), (N_, P, D)), (3, (3, 1, 2), (P, N_, N_)), (4, (2, 3, 1), (P, P, N_)),
+                                        (5, (1, 1, 3), (N_, N_, D)), (2, (4, 1, 6), (P, N_, N_))])
+def test_poisson_on_a_neumann_axis_of_one_cell(p, cells, bc):
+    """The solves on such axes, with the bar of the other Poisson cases; where z
+    has room for conductors, the constrained solve too."""
+    import paper_2504_00998_amd as fe
+    print("case: poisson, one Neumann cell", p, cells, bc, flush=True)
+    L = tuple(float(c) for c in cells)
+    om, gm = O.Mesh(L, cells, p, bc), fe.Mesh(L, cells, p, bc)
+    s = np.random.default_rng(11).standard_normal(om.n)
+    sd = torch.from_numpy(s).cuda()
+    ref = O.poisson(om, s)
+    phi, it, rel = gm.poisson(sd, tol=1e-13)
+    assert rel <= 1e-13 and it > 0
+    assert np.abs(phi.cpu().numpy() - ref).max() <= 1e-8 * np.abs(ref).max()
+    if cells[2] >= 6:
+        ref = O.poisson_cpd(om, s, np.zeros(om.n), 1.2, 4.9, 0.3)
+        phi, it, rel = gm.poisson_cpd(sd, 1.2, 4.9, 0.3, tol=1e-13)
+        assert rel <= 1e-13 and np.abs(phi.cpu().numpy() - ref).max() <= 1e-8 * np.abs(ref).max()
