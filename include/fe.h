@@ -96,8 +96,9 @@ fe_status fe_mesh_destroy(fe_mesh *mesh);
  * which applies the stiffness axis by axis in one launch, for blocks of three
  * vectors or more on meshes without a zero-Neumann axis (p = 3 and 4; the
  * other degrees from 64 cells on), as long as one z plane of a block is below
- * 2 GiB; its form for one or two vectors on meshes of 1024 cells and more, with
- * any boundary conditions; the kernels below elsewhere.  1 = one cell x 16 vectors per
+ * 1 GiB (2 GiB for a complex block); its form for one or two vectors on meshes
+ * of 1024 cells and more, with any boundary conditions; the kernels below
+ * elsewhere.  1 = one cell x 16 vectors per
  * workgroup, cell matrix streamed from L2 (the plain reference form);
  * 3 / 4 = one cell x 32 / 64 vectors per workgroup, so each cell-matrix
  * fragment read from L2 feeds 2 / 4 products (falls back to 1 when the block
@@ -130,7 +131,7 @@ fe_status fe_mesh_destroy(fe_mesh *mesh);
  * In the Bloch mode (the _k entry points at k != 0) variants 0 and 10 run
  * the tensor-product kernel with the k.G term, at every degree, where it
  * applies (no zero-Neumann axis, a plane below 2 GiB); the row-owner kernel
- * there and for the other variants.
+ * elsewhere and for the other variants.
  * Variants 2 (register-resident), 5 (tiles of cells) and 8
  * (warp-specialised), slower than the defaults everywhere, were removed:
  * FE_EINVAL for them and for values outside 0..10. */
@@ -366,7 +367,8 @@ fe_status fe_poisson_solve_cpd(fe_mesh *mesh, const double *charge, const double
 
 /* Set the wave vector (k_x, k_y) (bohr^-1) used by the _k entry points;
  * (0, 0) is the Gamma point, where they equal the real entry points applied
- * to the real and imaginary parts (bitwise).  FE_EINVAL for a non-finite k
+ * to the real and imaginary parts (bitwise; under variant 10, whose conditions
+ * look at columns and leading dimensions, to rounding).  FE_EINVAL for a non-finite k
  * or a nonzero component along a non-periodic axis.  Waits for the device,
  * then builds the k.G cell fragments and projector phases (synchronous). */
 fe_status fe_set_kpoint(fe_mesh *mesh, double kx, double ky);

@@ -2262,10 +2262,11 @@ static hipError_t launch_step_v(const fe_mesh *m, const StepArgs &a, fe_dtype pr
     if (prec == FE_F64 && tensor_applies(m, a) &&
         (variant == 0 ? tensor_default(m, a) : variant == 10 && (a.S || (a.N >= 32 && dma_applies(m, a, prec)))))
         return launch_tensor(m, a, s);
-    // one or two columns on a mesh of 1024 cells or more (24 us against 97 at
+    // one or two vectors on a mesh of 1024 cells or more (24 us against 97 at
     // p = 4, 24x24x48 cells; below 1024 cells the default equals the one-cell
     // kernel bit for bit)
-    if (prec == FE_F64 && variant == 0 && (a.vectors ? a.vectors : a.N) < 3 && m->ncells >= 1024 && tensor_vec_applies(m, a))
+    const int64_t vectors = a.vectors ? a.vectors : a.N;
+    if (prec == FE_F64 && variant == 0 && vectors < 3 && m->ncells >= 1024 && tensor_vec_applies(m, a))
         return launch_tensor_vec(m, a, s);
     StepParams prm;
     prm.X = a.X; prm.ldx = a.ldx;
@@ -2340,7 +2341,9 @@ static hipError_t launch_step_v(const fe_mesh *m, const StepArgs &a, fe_dtype pr
     // against 5.9-6.1 for the one-cell pipelined kernel, FP32 4.24 against
     // 5.8, BF16 3.84 against 5.0 for the multi-chunk kernel, ms per H~X on
     // the 24x24x48-cell slab, 256 vectors)
-    const bool zseg = variant == 9 || (variant == 0 && m->p == 4);
+    // (a complex vector at the Gamma point takes the order of sums of its real
+    // and imaginary parts, which one column at a time run the one-cell kernel)
+    const bool zseg = variant == 9 || (variant == 0 && m->p == 4 && !(prec == FE_F64 && vectors == 1));
     if (variant == 7 && prec != FE_BF16) {
 #define FE_PIPE(PP)                                                                       \
     case PP:                                                                              \

@@ -668,15 +668,26 @@ static hipError_t launch_tensor_p(const fe_mesh *m, const StepArgs &a, hipStream
     return hipGetLastError();
 }
 
+// Whether a plane of every block lies within the 31 bits of its buffer requests
+// (a byte offset past them is what an absent row requests).  At the Gamma point
+// the columns are complex vectors' real and imaginary parts, and the line is
+// that of the parts' own blocks with half the leading dimension, or the
+// results would not be the parts' bit for bit: so a real block has to leave
+// the room for its complex one, 1 GiB a plane (below that line the kernel's
+// plane ranges hold either; larger planes run the cell kernels).
+static bool planes_in_range(const fe_mesh *m, const StepArgs &a) {
+    const bool pairs = a.S || (a.vectors && a.vectors != a.N);
+    const int64_t plane = m->nf[0] * m->nf[1], ld = std::max(std::max(a.ldx, a.ldy), a.Ym1 ? a.ldm : (int64_t)0);
+    return ld <= (int64_t)0x7FFFFFFF / 16 / plane * (pairs ? 2 : 1);
+}
+
 // Whether the tensor-product form applies: no zero-Neumann axis (M^-1/2 of a
 // node is then a product of factors of its local indices, the same in every
-// cell), a plane of every block within the 31 bits of its buffer requests,
-// and a recurrence whose beta / alpha is a number.
+// cell), planes in range, and a recurrence whose beta / alpha is a number.
 bool tensor_applies(const fe_mesh *m, const StepArgs &a) {
     for (int d = 0; d < 3; ++d)
         if (m->bc[d] == FE_BC_NEUMANN) return false;
-    const int64_t plane = m->nf[0] * m->nf[1], ld = std::max(std::max(a.ldx, a.ldy), a.Ym1 ? a.ldm : (int64_t)0);
-    if (ld > (int64_t)0x7FFFFFFF / 8 / plane) return false;
+    if (!planes_in_range(m, a)) return false;
     if (a.N >= (int64_t)1 << 31) return false;
     return a.alpha != 0.0 && std::isfinite(a.beta / a.alpha);
 }
@@ -1093,12 +1104,12 @@ static hipError_t launch_vec_p(const fe_mesh *m, const StepArgs &a, hipStream_t 
     return hipGetLastError();
 }
 
-// One or two columns.  part (not null): also the partial sums of x times y over
-// the workgroups, *nparts of them (at most max_parts), unless *done is nonzero.
+// One or two vectors, real or (at the Gamma point) complex.  part (not null):
+// also the partial sums of x times y over the workgroups, *nparts of them (at
+// most max_parts), unless *done is nonzero.
 bool tensor_vec_applies(const fe_mesh *m, const StepArgs &a) {
-    if (a.S || a.N < 1 || a.N > 2) return false;
-    const int64_t plane = m->nf[0] * m->nf[1], ld = std::max(std::max(a.ldx, a.ldy), a.Ym1 ? a.ldm : (int64_t)0);
-    if (ld > (int64_t)0x7FFFFFFF / 8 / plane) return false;
+    if (a.S || a.N < 1 || (a.vectors ? a.vectors : a.N) > 2) return false;
+    if (!planes_in_range(m, a)) return false;
     return a.alpha != 0.0 && std::isfinite(a.beta / a.alpha);
 }
 

@@ -237,3 +237,53 @@ def test_poisson_on_a_neumann_axis_of_one_cell(p, cells, bc):
         ref = O.poisson_cpd(om, s, np.zeros(om.n), 1.2, 4.9, 0.3)
         phi, it, rel = gm.poisson_cpd(sd, 1.2, 4.9, 0.3, tol=1e-13)
         assert rel <= 1e-13 and np.abs(phi.cpu().numpy() - ref).max() <= 1e-8 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("p,cells,bc,N", [(4, (5, 5, 6), (P, P, D), 1), (4, (4, 3, 5), (P, P, D), 2), (4, (8, 8, 16), (P, P, D), 1),
+                                          (4, (8, 8, 16), (P, P, D), 2), (4, (8, 8, 16), (P, P, D), 3),
+                                          (2, (16, 17, 4), (P, P, N_), 2), (6, (4, 16, 16), (P, D, P), 2),
+                                          (3, (16, 8, 8), (D, D, D), 1), (5, (4, 4, 4), (P, P, D), 2)])
+def test_gamma_point_equals_real_path_at_every_width(p, cells, bc, N):
+    """One to three complex vectors at k = 0, on both sides of the 1024 cells from
+    which one and two vectors take the single-vector kernel: bit for bit the
+    real entry points on the real and imaginary parts."""
+    import paper_2504_00998_amd as fe
+    wl = W.small_slab(cells, p=p, N=N, m=5, bc=bc, **({"E": 0.0} if bc[2] == P else {}))
+    print("case: gamma", p, cells, bc, N, flush=True)
+    gm = fe.Mesh.from_workload(wl)
+    gm.set_potential(torch.from_numpy(W.workload_potential(wl, gm.quad_points())).cuda(), wl.E, wl.z0)
+    X = torch.from_numpy(wl.Xc(gm.n)).cuda()
+    Xr, Xi = X.real.contiguous(), X.imag.contiguous()
+    Y = gm.hx_k(X)
+    assert torch.equal(Y.real, gm.hx(Xr)) and torch.equal(Y.imag, gm.hx(Xi))
+    Y = gm.cheb_filter_k(X, 5, 3.0, 900.0, -1.0)
+    assert torch.equal(Y.real, gm.cheb_filter(Xr, 5, 3.0, 900.0, -1.0))
+    assert torch.equal(Y.imag, gm.cheb_filter(Xi, 5, 3.0, 900.0, -1.0))
+
+
+@pytest.mark.parametrize("gib", [0.9, 1.1, 1.9])
+def test_gamma_point_equals_real_path_at_wide_rows(gib):
+    """Three vectors in rows so wide that a z plane of the real block has 0.9, 1.1
+    and 1.9 GiB (twice that the complex one): both take the same kernel on
+    either side of the line, and the values are those of narrow rows."""
+    import paper_2504_00998_amd as fe
+    wl = W.small_slab((2, 2, 1), p=3, N=3)
+    plane = 36
+    ld = int(gib * 2**30) // (8 * plane)
+    print("case: gamma, wide rows", gib, ld, flush=True)
+    gm = fe.Mesh.from_workload(wl)
+    gm.set_potential(torch.from_numpy(W.workload_potential(wl, gm.quad_points())).cuda(), wl.E, wl.z0)
+    assert gm.n == 2 * plane
+    Xc = torch.from_numpy(wl.Xc(gm.n)).cuda()
+    X = torch.empty((gm.n, ld), dtype=torch.complex128, device="cuda")[:, :3]
+    X.copy_(Xc)
+    Y = gm.hx_k(X).contiguous()
+    del X
+    narrow = gm.hx_k(Xc)
+    assert float((Y - narrow).abs().max()) < 1e-13 * float(narrow.abs().max())
+    Xr = torch.empty((gm.n, ld), dtype=torch.float64, device="cuda")[:, :3]
+    Xr.copy_(Xc.real)
+    assert torch.equal(Y.real, gm.hx(Xr).contiguous())
+    Xr.copy_(Xc.imag)
+    assert torch.equal(Y.imag, gm.hx(Xr).contiguous())
+    torch.cuda.empty_cache()
