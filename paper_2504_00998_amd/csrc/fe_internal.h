@@ -149,13 +149,17 @@ struct StepArgs {
     int64_t vectors = 0;        // vectors the columns are (complex ones count once; 0: N)
 };
 
-// the step in tensor-product form (fe_tensor.hip), FP64
+// the step in tensor-product form, FP64 (rules and launch by degree: fe_tensor_rules.cpp; kernels: fe_tensor.hip)
 bool tensor_applies(const fe_mesh *m, const StepArgs &a);
 bool tensor_default(const fe_mesh *m, const StepArgs &a);
 hipError_t launch_tensor(const fe_mesh *m, const StepArgs &a, hipStream_t s);
 bool tensor_vec_applies(const fe_mesh *m, const StepArgs &a);
 hipError_t launch_tensor_vec(const fe_mesh *m, const StepArgs &a, hipStream_t s, const double *done = nullptr,
                              double *part = nullptr, int max_parts = 0, int *nparts = nullptr);
+template <int P> hipError_t launch_tensor_degree(const fe_mesh *m, const StepArgs &a, hipStream_t s);
+template <int P>
+hipError_t launch_vec_degree(const fe_mesh *m, const StepArgs &a, hipStream_t s, const double *done, double *part,
+                             int max_parts, int *nparts);
 hipError_t launch_step(const fe_mesh *m, const StepArgs &a, fe_dtype prec, hipStream_t s);
 hipError_t launch_potential(const fe_mesh *m, const double *Vq, double E, double z0, hipStream_t s);
 hipError_t launch_potential_vjp(const fe_mesh *m, const double *g, double z0, double *Vbar, double *Ebar,

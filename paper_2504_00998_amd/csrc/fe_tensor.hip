@@ -668,45 +668,6 @@ static hipError_t launch_tensor_p(const fe_mesh *m, const StepArgs &a, hipStream
     return hipGetLastError();
 }
 
-// Whether a plane of every block lies within the 31 bits of its buffer requests
-// (a byte offset past them is what an absent row requests).  At the Gamma point
-// the columns are complex vectors' real and imaginary parts, and the line is
-// that of the parts' own blocks with half the leading dimension, or the
-// results would not be the parts' bit for bit: so a real block has to leave
-// the room for its complex one, 1 GiB a plane (below that line the kernel's
-// plane ranges hold either; larger planes run the cell kernels).
-static bool planes_in_range(const fe_mesh *m, const StepArgs &a) {
-    const bool pairs = a.S || (a.vectors && a.vectors != a.N);
-    const int64_t plane = m->nf[0] * m->nf[1], ld = std::max(std::max(a.ldx, a.ldy), a.Ym1 ? a.ldm : (int64_t)0);
-    return ld <= (int64_t)0x7FFFFFFF / 16 / plane * (pairs ? 2 : 1);
-}
-
-// Whether the tensor-product form applies: no zero-Neumann axis (M^-1/2 of a
-// node is then a product of factors of its local indices, the same in every
-// cell), planes in range, and a recurrence whose beta / alpha is a number.
-bool tensor_applies(const fe_mesh *m, const StepArgs &a) {
-    for (int d = 0; d < 3; ++d)
-        if (m->bc[d] == FE_BC_NEUMANN) return false;
-    if (!planes_in_range(m, a)) return false;
-    if (a.N >= (int64_t)1 << 31) return false;
-    return a.alpha != 0.0 && std::isfinite(a.beta / a.alpha);
-}
-
-// Where it is the default.  It is faster than the cell kernels at every size
-// measured, so the line is drawn by what else holds:
-// the default of the other degrees on a few cells, and of one or two vectors
-// up to a mesh of the size where Lanczos and CG spend time on the product,
-// are documented to equal the one-cell kernel (variant 1) bit for bit.  The
-// rule looks at the number of vectors, not of real columns, so that a complex
-// block at the Gamma point takes the kernel of its real and imaginary parts; at
-// other k-points (no such equality there) it has no line.
-bool tensor_default(const fe_mesh *m, const StepArgs &a) {
-    if (a.S) return true;
-    const int64_t vectors = a.vectors ? a.vectors : a.N;
-    if (vectors < 3) return false;
-    return m->p == 3 || m->p == 4 || m->ncells >= 64;
-}
-
 // Tile shapes (BX, BY cells, XC cells per x item, waves per SIMD), the fastest
 // of six to ten each on the slabs above (ms per step on whole / ragged
 // 128-byte rows): p = 4 (2, 4) 2.50 / 1.25, (2, 3) 2.46 / 1.30, (3, 3) 2.45 /
@@ -715,21 +676,17 @@ bool tensor_default(const fe_mesh *m, const StepArgs &a) {
 // (1, 2) 2.87 / 3.37; p = 3 (2, 6) 0.39 / 0.49, (2, 4) 0.40 / 0.51, (4, 3) 0.42 /
 // 0.53; p = 7 (1, 1) 0.60 / 0.66, (1, 2) 0.68 / 0.71.  Two waves on a cell's rows
 // (half the output planes each) were no faster at any degree.
-hipError_t launch_tensor(const fe_mesh *m, const StepArgs &a, hipStream_t s) {
-#define FE_TENSOR(PP, BX, BY, XC, OCC, CBX, CBY, CXC, COCC)                             \
-    case PP:                                                                            \
-        return a.S ? launch_tensor_p<PP, CBX, CBY, CXC, COCC, true>(m, a, s)            \
-                   : launch_tensor_p<PP, BX, BY, XC, OCC, false>(m, a, s);
-    switch (m->p) {
-        FE_TENSOR(1, 4, 8, 2, 4, 4, 8, 2, 4)
-        FE_TENSOR(2, 3, 6, 3, 4, 3, 6, 3, 4)
-        FE_TENSOR(3, 2, 6, 2, 3, 2, 6, 2, 3)
-        FE_TENSOR(4, 2, 4, 2, 3, 2, 4, 2, 3)
-        FE_TENSOR(5, 1, 4, 1, 3, 1, 4, 1, 3)
-        FE_TENSOR(6, 1, 2, 1, 2, 1, 2, 1, 2)
-        FE_TENSOR(7, 1, 1, 1, 2, 1, 1, 1, 2)
-    default: return hipErrorInvalidValue;
-    }
+template <int P> hipError_t launch_tensor_degree(const fe_mesh *m, const StepArgs &a, hipStream_t s) {
+#define FE_TENSOR(PP, BX, BY, XC, OCC)                                             \
+    if constexpr (P == PP)                                                         \
+        return a.S ? launch_tensor_p<PP, BX, BY, XC, OCC, true>(m, a, s) : launch_tensor_p<PP, BX, BY, XC, OCC, false>(m, a, s);
+    FE_TENSOR(1, 4, 8, 2, 4)
+    FE_TENSOR(2, 3, 6, 3, 4)
+    FE_TENSOR(3, 2, 6, 2, 3)
+    FE_TENSOR(4, 2, 4, 2, 3)
+    FE_TENSOR(5, 1, 4, 1, 3)
+    FE_TENSOR(6, 1, 2, 1, 2)
+    FE_TENSOR(7, 1, 1, 1, 2)
 #undef FE_TENSOR
 }
 
@@ -1104,36 +1061,35 @@ static hipError_t launch_vec_p(const fe_mesh *m, const StepArgs &a, hipStream_t 
     return hipGetLastError();
 }
 
-// One or two vectors, real or (at the Gamma point) complex.  part (not null):
-// also the partial sums of x times y over the workgroups, *nparts of them (at
-// most max_parts), unless *done is nonzero.
-bool tensor_vec_applies(const fe_mesh *m, const StepArgs &a) {
-    if (a.S || a.N < 1 || (a.vectors ? a.vectors : a.N) > 2) return false;
-    if (!planes_in_range(m, a)) return false;
-    return a.alpha != 0.0 && std::isfinite(a.beta / a.alpha);
+template <int P>
+hipError_t launch_vec_degree(const fe_mesh *m, const StepArgs &a, hipStream_t s, const double *done, double *part,
+                             int max_parts, int *nparts) {
+    constexpr int BX = P == 1 ? 32 : P == 2 ? 16 : P <= 4 ? 8 : 4, BY = 8;
+    const bool neu = m->bc[0] == FE_BC_NEUMANN || m->bc[1] == FE_BC_NEUMANN || m->bc[2] == FE_BC_NEUMANN;
+    if (part)
+        return neu ? launch_vec_p<P, BX, BY, true, true>(m, a, s, done, part, max_parts, nparts)
+                   : launch_vec_p<P, BX, BY, false, true>(m, a, s, done, part, max_parts, nparts);
+    return neu ? launch_vec_p<P, BX, BY, true, false>(m, a, s, nullptr, nullptr, 0, nullptr)
+               : launch_vec_p<P, BX, BY, false, false>(m, a, s, nullptr, nullptr, 0, nullptr);
 }
 
-hipError_t launch_tensor_vec(const fe_mesh *m, const StepArgs &a, hipStream_t s, const double *done, double *part,
-                             int max_parts, int *nparts) {
-    const bool neu = m->bc[0] == FE_BC_NEUMANN || m->bc[1] == FE_BC_NEUMANN || m->bc[2] == FE_BC_NEUMANN;
-#define FE_VEC(PP, BX, BY)                                                                                        \
-    case PP:                                                                                                      \
-        if (part)                                                                                                 \
-            return neu ? launch_vec_p<PP, BX, BY, true, true>(m, a, s, done, part, max_parts, nparts)             \
-                       : launch_vec_p<PP, BX, BY, false, true>(m, a, s, done, part, max_parts, nparts);           \
-        return neu ? launch_vec_p<PP, BX, BY, true, false>(m, a, s, nullptr, nullptr, 0, nullptr)                 \
-                   : launch_vec_p<PP, BX, BY, false, false>(m, a, s, nullptr, nullptr, 0, nullptr);
-    switch (m->p) {
-        FE_VEC(1, 32, 8)
-        FE_VEC(2, 16, 8)
-        FE_VEC(3, 8, 8)
-        FE_VEC(4, 8, 8)
-        FE_VEC(5, 4, 8)
-        FE_VEC(6, 4, 8)
-        FE_VEC(7, 4, 8)
-    default: return hipErrorInvalidValue;
-    }
-#undef FE_VEC
-}
+// Every degree in one object, or with FE_TENSOR_DEGREE that one: the unrolled
+// walks take the compiler longer than the rest of the library, so build.py
+// compiles the degrees side by side.
+#define FE_DEGREE(PP)                                                                                              \
+    template hipError_t launch_tensor_degree<PP>(const fe_mesh *, const StepArgs &, hipStream_t);                  \
+    template hipError_t launch_vec_degree<PP>(const fe_mesh *, const StepArgs &, hipStream_t, const double *, double *, int, int *);
+#ifdef FE_TENSOR_DEGREE
+FE_DEGREE(FE_TENSOR_DEGREE)
+#else
+FE_DEGREE(1)
+FE_DEGREE(2)
+FE_DEGREE(3)
+FE_DEGREE(4)
+FE_DEGREE(5)
+FE_DEGREE(6)
+FE_DEGREE(7)
+#endif
+#undef FE_DEGREE
 
 }  // namespace fe
