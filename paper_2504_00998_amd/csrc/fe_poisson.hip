@@ -153,9 +153,9 @@ __device__ __forceinline__ void cg_walk(const CgWalk &t, const double *__restric
         const double exy = t.singular ? (mx * tab[tx]) * (my * tab[F + ty]) * t.ie : 0.0;
         const int64_t plane = (int64_t)t.nfx * t.nfy, i0 = (int64_t)ty * t.nfx + tx;
         for (int z = z0; z < z1; z += U) {
-    #pragma unroll
+#pragma unroll
             for (int u = 0; u < U; ++u) load(u, i0 + plane * min(z + u, z1 - 1));
-    #pragma unroll
+#pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int tz = min(z + u, z1 - 1);
                 const double mz = tab[8 * F + tz], kz = tab[11 * F + tz], dz = tab[14 * F + tz], zc = zcoord[tz];
@@ -171,8 +171,9 @@ __device__ __forceinline__ void cg_walk(const CgWalk &t, const double *__restric
 // in the same order); r -= alpha q, and the partial sums r.r, r.z, e.z, r.e with
 // z = pinv r (before the null-space projection).  p.q <= 0 stops the iteration.
 __global__ __launch_bounds__(kRedThreads) void cg_update_kernel(double *__restrict__ r, const double *__restrict__ q,
-                                                                CgWalk t, const double *__restrict__ tab, const double *__restrict__ zcoord, double *sc, int rzi, const double *pq, int npq,
-                                                                double *part) {
+                                                                CgWalk t, const double *__restrict__ tab,
+                                                                const double *__restrict__ zcoord, double *sc, int rzi,
+                                                                const double *pq, int npq, double *part) {
     __shared__ double lds[4 * kRedWaves], lds1[kRedWaves];
     if (sc[S_DONE] != 0.0) {
         if (blockIdx.x == 0 && threadIdx.x == 0) sc[S_STOP] = 1.0;
@@ -214,7 +215,9 @@ __global__ __launch_bounds__(kRedThreads) void cg_update_kernel(double *__restri
 // Each of the two flags is read by one kind of launch and set by the other (S_DONE
 // here, S_STOP by the update), so all threads of a launch see the same value.
 __global__ __launch_bounds__(kRedThreads) void cg_direction_kernel(double *__restrict__ x, double *__restrict__ p,
-                                                                   const double *__restrict__ r, CgWalk t, const double *__restrict__ tab, const double *__restrict__ zcoord,
+                                                                   const double *__restrict__ r, CgWalk t,
+                                                                   const double *__restrict__ tab,
+                                                                   const double *__restrict__ zcoord,
                                                                    const double *part, int nb, double *sc, int rzi) {
     __shared__ double lds[4 * kRedWaves];
     if (sc[S_STOP] != 0.0) {
@@ -444,10 +447,11 @@ fe_status poisson_solve(fe_mesh *m, const double *charge, double *phi, double to
             StepArgs a{p, 1, q, 1, nullptr, 0, 1.0, 0.0, 0.0, 1, zero};
             int nq = 0;
             const int most = (int)std::min<int64_t>(n, kRedBlocks);
-            if (!tensor_vec_applies(m, a) || launch_tensor_vec(m, a, ss, sc + S_DONE, z, most, &nq) != hipSuccess) {
-                (void)hipGetLastError();
-                hipError_t e2 = launch_step(m, a, FE_F64, ss);
-                if (e2 != hipSuccess) return e2;
+            hipError_t e2 = tensor_vec_applies(m, a) ? launch_tensor_vec(m, a, ss, sc + S_DONE, z, most, &nq) : hipSuccess;
+            if (e2 != hipSuccess) return e2;
+            if (nq == 0) {
+                // planes out of the kernel's range, or more tiles than partial sums
+                if ((e2 = launch_step(m, a, FE_F64, ss)) != hipSuccess) return e2;
                 nq = nb;
                 hipLaunchKernelGGL(cg_pq_kernel, dim3(nb), dim3(kRedThreads), 0, ss, p, q, n, sc, z);
             }

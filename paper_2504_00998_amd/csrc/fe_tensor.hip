@@ -1053,10 +1053,14 @@ static hipError_t launch_vec_p(const fe_mesh *m, const StepArgs &a, hipStream_t 
     while (DOT && k.layers < k.last && (int64_t)k.ntx * k.nty * ((k.last + k.layers - 1) / k.layers) > max_parts) ++k.layers;
     k.nzc = (k.last + k.layers - 1) / k.layers;
     const int64_t blocks = (int64_t)k.ntx * k.nty * k.nzc;
-    if (blocks > (1 << 30) || (DOT && blocks > max_parts)) return hipErrorInvalidValue;
+    if (DOT) {
+        // (more tiles than partial sums: nothing is launched)
+        *nparts = blocks > max_parts ? 0 : (int)blocks;
+        if (*nparts == 0) return hipSuccess;
+    }
+    if (blocks > (1 << 30)) return hipErrorInvalidValue;
     k.done = done;
     k.part = part;
-    if (nparts) *nparts = (int)blocks;
     hipLaunchKernelGGL((tensor_vec_kernel<P, BX, BY, NEU, DOT>), dim3((unsigned)blocks, (unsigned)a.N), dim3(S::T), 0, s, k);
     return hipGetLastError();
 }

@@ -66,8 +66,9 @@ hipError_t launch_tensor(const fe_mesh *m, const StepArgs &a, hipStream_t s) {
 }
 
 // One or two vectors, real or (at the Gamma point) complex.  part (not null):
-// also the partial sums of x times y over the workgroups, *nparts of them (at
-// most max_parts), unless *done is nonzero.
+// also the partial sums of x times y over the workgroups, *nparts of them,
+// unless *done is nonzero; where the tiles are more than max_parts, *nparts is
+// zero and nothing is launched.
 bool tensor_vec_applies(const fe_mesh *m, const StepArgs &a) {
     if (a.S || a.N < 1 || (a.vectors ? a.vectors : a.N) > 2) return false;
     if (!planes_in_range(m, a)) return false;

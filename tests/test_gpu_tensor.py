@@ -287,3 +287,50 @@ def test_gamma_point_equals_real_path_at_wide_rows(gib):
     Xr.copy_(Xc.imag)
     assert torch.equal(Y.imag, gm.hx(Xr).contiguous())
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("p,cells,bc", [(1, (3, 4, 5), (P, N_, P)), (6, (2, 3, 2), (P, P, N_)), (7, (2, 2, 3), (N_, P, D)),
+                                        (7, (2, 3, 2), (P, P, N_))])
+def test_poisson_at_the_other_degrees(p, cells, bc):
+    """Conjugate gradients with the product's own partial sums at p = 1, 6 and 7."""
+    import paper_2504_00998_amd as fe
+    print("case: poisson", p, cells, bc, flush=True)
+    L = tuple(float(c) for c in cells)
+    om, gm = O.Mesh(L, cells, p, bc), fe.Mesh(L, cells, p, bc)
+    s = np.random.default_rng(12).standard_normal(om.n)
+    ref = O.poisson(om, s)
+    phi, it, rel = gm.poisson(torch.from_numpy(s).cuda(), tol=1e-13)
+    assert rel <= 1e-13 and it > 0
+    assert np.abs(phi.cpu().numpy() - ref).max() <= 1e-8 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("p,cells,bc", [(1, (64, 63, 129), (P, P, D)), (2, (64, 63, 65), (P, P, D)), (4, (48, 47, 49), (P, P, N_)),
+                                        (7, (16, 33, 40), (P, P, D)), (1, (1056, 250, 2), (P, P, D))])
+def test_poisson_with_more_layers_than_partial_sums(p, cells, bc):
+    """More (tile, layer) items than partial sums of p.Hp, so that a workgroup walks
+    several layers, and (last) more tiles than partial sums, where the product
+    and its dot product are launches of their own: the residual of the scaled
+    equation H0 x = 2 pi M^1/2 s by the one-cell kernel.  The solve's recurrence
+    ends at 1e-11; the residual formed anew differs from it by the rounding of
+    the iterates, eps |H0| |x| / |b| an iteration at most and less than 1e-9 over
+    all (|H0| below 2e3, |x| / |b| about 10 for random charges)."""
+    import paper_2504_00998_amd as fe
+    print("case: poisson, layers", p, cells, bc, flush=True)
+    L = tuple(float(c) for c in cells)
+    gm = fe.Mesh(L, cells, p, bc)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(p)
+    s = torch.randn(gm.n, generator=g, dtype=torch.float64, device="cuda")
+    phi, it, rel = gm.poisson(s, tol=1e-11)
+    print("iterations", it, "relres", rel, flush=True)
+    assert 0 < it < 100000 and rel <= 1e-11
+    root = torch.from_numpy(np.sqrt(O.Mesh(L, cells, p, bc).mass())).cuda()
+    b = 2.0 * math.pi * root * s
+    if D not in bc:
+        e = root / root.norm()
+        b -= (e @ b) * e
+        assert abs(float(root @ (root * phi))) < 1e-10 * float(phi.abs().max()) * float(root @ root)
+    gm.set_potential(None, 0.0, 0.0)
+    gm.set_kernel(1)
+    r = gm.hx((root * phi).reshape(-1, 1)).reshape(-1) - b
+    assert float(r.norm() / b.norm()) < 1e-9
