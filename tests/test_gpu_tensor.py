@@ -289,6 +289,53 @@ def test_gamma_point_equals_real_path_at_wide_rows(gib):
     torch.cuda.empty_cache()
 
 
+def _device_mesh(p, cells, bc):
+    import paper_2504_00998_amd as fe
+    gm = fe.Mesh(tuple(float(c) for c in cells), cells, p, bc)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(100 * p + cells[2])
+    gm.set_potential(torch.randn((gm.n_cells, gm.nc), generator=g, dtype=torch.float64, device="cuda"), 0.0, 0.0)
+    return gm, g
+
+
+def _against_one_cell_kernel(gm, X, m=4):
+    """Product and filter against variant 1 (itself held to 1e-13 and 1e-12 of the
+    oracle, as the kernel under test is: twice that between the two)."""
+    def err(A, B):
+        return float(((A - B).norm(dim=0) / B.norm(dim=0)).max())
+
+    got = gm.hx(X), gm.cheb_filter(X, m, 3.0, 900.0, -1.0)
+    gm.set_kernel(1)
+    ref = gm.hx(X), gm.cheb_filter(X, m, 3.0, 900.0, -1.0)
+    gm.set_kernel(0)
+    assert err(got[0], ref[0]) < 2e-13 and err(got[1], ref[1]) < 2e-12
+
+
+@pytest.mark.parametrize("p,cells,bc,N,pad", [(1, (64, 63, 17), (P, P, D), 64, 0), (2, (30, 31, 17), (P, P, P), 64, 0),
+                                              (3, (24, 25, 17), (D, P, D), 64, 0), (4, (24, 22, 13), (P, P, D), 64, 0),
+                                              (5, (12, 13, 11), (P, D, P), 64, 0), (6, (12, 11, 11), (P, P, D), 64, 0),
+                                              (7, (16, 31, 9), (P, P, D), 64, 0), (2, (30, 31, 17), (P, P, D), 50, 3),
+                                              (7, (16, 31, 9), (P, P, P), 50, 3)])
+def test_tensor_kernel_walks_several_layers(p, cells, bc, N, pad):
+    """More (tile, column group, layer) items than workgroups at once, so that a
+    workgroup closes several of its own layers: sums carried from one to the
+    next, the previous iterate's register sets in turn, and several column
+    groups on whole and on ragged 128-byte rows."""
+    print("case: layers", p, cells, bc, N, pad, flush=True)
+    gm, g = _device_mesh(p, cells, bc)
+    X = torch.randn((gm.n, N + pad), generator=g, dtype=torch.float64, device="cuda")[:, :N]
+    _against_one_cell_kernel(gm, X)
+
+
+@pytest.mark.parametrize("p,cells,bc", [(1, (64, 63, 400), (P, P, D)), (2, (64, 65, 127), (P, P, N_)), (3, (48, 49, 65), (N_, P, P)),
+                                        (4, (48, 47, 65), (P, P, D)), (6, (16, 33, 81), (P, D, N_)), (7, (16, 33, 81), (P, P, D))])
+def test_single_vector_kernel_walks_several_layers(p, cells, bc):
+    """The same for one vector."""
+    print("case: layers, one vector", p, cells, bc, flush=True)
+    gm, g = _device_mesh(p, cells, bc)
+    _against_one_cell_kernel(gm, torch.randn((gm.n, 1), generator=g, dtype=torch.float64, device="cuda"))
+
+
 @pytest.mark.parametrize("p,cells,bc", [(1, (3, 4, 5), (P, N_, P)), (6, (2, 3, 2), (P, P, N_)), (7, (2, 2, 3), (N_, P, D)),
                                         (7, (2, 3, 2), (P, P, N_))])
 def test_poisson_at_the_other_degrees(p, cells, bc):
