@@ -381,3 +381,27 @@ def test_poisson_with_more_layers_than_partial_sums(p, cells, bc):
     gm.set_kernel(1)
     r = gm.hx((root * phi).reshape(-1, 1)).reshape(-1) - b
     assert float(r.norm() / b.norm()) < 1e-9
+
+
+@pytest.mark.parametrize("p,cells,bc,variant", [(p, (3, 2, 3), (P, P, D), 1) for p in range(1, 8)] +
+                         [(3, (3, 4, 3), (P, P, N_), 0), (5, (2, 3, 2), (P, D, N_), 0), (4, (4, 4, 4), (P, P, P), 6)])
+def test_bloch_row_owner_kernel_matches_oracle(p, cells, bc, variant):
+    """Bloch mode where the tensor-product kernel is not taken: the other variants
+    at every degree, and a zero-Neumann z axis by default."""
+    import paper_2504_00998_amd as fe
+    wl = W.small_slab(cells, p=p, N=9, m=4, bc=bc, **({"E": 0.0} if bc[2] == P else {}))
+    print("case: bloch, row owner", p, cells, bc, variant, flush=True)
+    om = O.Mesh.from_workload(wl)
+    Vq = W.workload_potential(wl, om.quad_points())
+    op = O.Operator(om, Vq, wl.E, wl.z0)
+    gm = fe.Mesh.from_workload(wl)
+    gm.set_potential(torch.from_numpy(Vq).cuda(), wl.E, wl.z0)
+    gm.set_kernel(variant)
+    k = (0.37, -0.61 if bc[1] == P else 0.0)
+    gm.set_kpoint(*k)
+    B = O.BlochOperator(op, om, k)
+    Xh = wl.Xc(op.n)
+    X = torch.from_numpy(Xh).cuda()
+    for Yd, R, bar in ((gm.hx_k(X), B.apply(Xh), 1e-13),
+                       (gm.cheb_filter_k(X, 4, 3.0, 900.0, -1.0), B.filter(Xh, 4, 3.0, 900.0, -1.0), 1e-12)):
+        assert (np.linalg.norm(Yd.cpu().numpy() - R, axis=0) / np.linalg.norm(R, axis=0)).max() < bar
