@@ -738,33 +738,25 @@ namespace {
 
 constexpr int kNeumann = 1;  // TensorAxis.per of a zero-Neumann axis
 
-// node of a zero-Neumann axis that node g of the even extension over its faces
-// is (negative where it is none)
-__device__ __forceinline__ int neumann_fold(const TensorAxis &a, int g) {
-    const int f = g < 0 ? -g : g;
-    return f > a.K ? 2 * a.K - f : f;
-}
-// free_node with zero-Neumann axes
+// free_node with zero-Neumann axes (the even extension over their faces)
 template <bool NEU> __device__ __forceinline__ int free_node_n(const TensorAxis &a, int g) {
     if constexpr (NEU) {
         if (a.per == kNeumann) {
-            const int f = neumann_fold(a, g);
+            int f = g < 0 ? -g : g;
+            f = f > a.K ? 2 * a.K - f : f;
             return f < 0 ? -1 : f;
         }
     }
     return free_node(a, g);
 }
-// whether node g of the extension is on a zero-Neumann face (on an axis of one
-// cell the reflected nodes -K and 2 K are too: each face is the other's
-// neighbour on both sides)
+// whether node g (of the axis itself) is on a zero-Neumann face
 template <bool NEU> __device__ __forceinline__ bool on_neumann_face(const TensorAxis &a, int g) {
-    if constexpr (NEU) {
-        if (a.per == kNeumann) {
-            const int f = neumann_fold(a, g);
-            return f == 0 || f == a.K;
-        }
-    }
-    return false;
+    return NEU && a.per == kNeumann && (g == 0 || g == a.K);
+}
+// whether node g of the extension is one on a zero-Neumann face: on an axis of
+// one cell the nodes -K and 2 K that it reaches are the opposite face's
+template <bool NEU> __device__ __forceinline__ bool is_neumann_face(const TensorAxis &a, int g) {
+    return on_neumann_face<NEU>(a, g) || (NEU && a.per == kNeumann && (g == -a.K || g == 2 * a.K));
 }
 // whether node g of cell c is one of the axis' outputs
 template <bool NEU> __device__ __forceinline__ bool axis_output(const TensorAxis &a, int c, int g) {
@@ -804,7 +796,7 @@ void tensor_vec_kernel(TensorVecParams<P> k) {
         const int fx = free_node_n<NEU>(k.ax[0], gx), fy = free_node_n<NEU>(k.ax[1], gy);
         off[q] = idx < RX * RY && fx >= 0 && fy >= 0 ? (uint32_t)(fy * k.ax[0].nfree + fx) * k.ldx + cb : kAbsent;
         if constexpr (NEU)
-            in_scale[q] = (on_neumann_face<NEU>(k.ax[0], gx) ? R2 : 1.0) * (on_neumann_face<NEU>(k.ax[1], gy) ? R2 : 1.0);
+            in_scale[q] = (is_neumann_face<NEU>(k.ax[0], gx) ? R2 : 1.0) * (is_neumann_face<NEU>(k.ax[1], gy) ? R2 : 1.0);
     }
     // y-z item: x position yx, cell yc
     const int yx = tid % WX, yc = min(tid / WX, BY - 1);
@@ -860,7 +852,8 @@ void tensor_vec_kernel(TensorVecParams<P> k) {
     };
     auto plane = [&](auto JJ, int g, bool flush) {
         constexpr int J = decltype(JJ)::value;
-        const double zin = NEU && on_neumann_face<NEU>(k.ax[2], g) ? R2 : 1.0;
+        // (faces are vertex planes)
+        const double zin = J == 0 && is_neumann_face<NEU>(k.ax[2], g) ? R2 : 1.0;
 #pragma unroll
         for (int q = 0; q < LR; ++q) {
             const int idx = tid + T * q, row = idx / RX, cx = idx % RX;
@@ -943,7 +936,7 @@ void tensor_vec_kernel(TensorVecParams<P> k) {
                     const int f = free_node_n<NEU>(k.ax[2], go) | (flush ? outside(go) : -1);
                     const __amdgpu_buffer_rsrc_t by = plane_of(k.Y, k.py, k.ry, f);
                     const uint32_t sy = (uint32_t)k.ax[0].nfree * k.ldy;
-                    const double zs = NEU && on_neumann_face<NEU>(k.ax[2], go) ? H2 : 1.0;
+                    const double zs = i == 0 && on_neumann_face<NEU>(k.ax[2], go) ? H2 : 1.0;
 #pragma unroll
                     for (int r = 0; r < P; ++r) {
                         double t = __builtin_fma(TK(i, P), A[r], __builtin_fma(TM(i, P), B[r], acc[i][r]));
