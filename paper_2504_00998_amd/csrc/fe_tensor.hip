@@ -34,21 +34,25 @@
 // beside it.  Each value of X, the previous iterate and Y moves once, but for
 // the X rows of the halo (a cell before and a node after the tile along x
 // and y), which the neighbouring workgroups of the same XCD read at about the
-// same time (11.6 GB counted per step of the p = 4 slab, 10.8 without a halo).
+// same time (12.07 GB counted per step of the p = 4 slab, 10.81 without a halo).
 //
 // What bounds it up to p = 4 is memory: with all arithmetic taken out the p = 4
-// slab's step took 2.30 ms, without the X rows 1.52.  X comes in 16-byte requests
+// slab's step was 4 % faster, without the X rows 37 %.  X comes in 16-byte requests
 // because a request of any width costs the address unit about the same (with
 // 8-byte ones it was busy 79 % of the time).  Above p = 4 the registers leave
-// room for few waves and the latency of a plane's stages shows.
+// room for few waves and the latency of a plane's stages shows (p = 6: the waves
+// wait 51 % of their cycles, the address units are busy 32 % of the time, no LDS
+// conflicts, 6.05 GB counted per step for 5.41 at 3.9 TB/s).  On rows that share
+// 128-byte lines the halo rows come from HBM again (p = 5, 200 vectors: a
+// product reads 7.2 GB for a block of 3.2).
 //
 // Measured, ms per recurrence step (two blocks read, one written), against the
 // kernels it replaces as the FP64 default: p = 4, 24x24x48 cells, 256 vectors
-// 2.47 (the table kernel 4.73) = 4.4 TB/s of the 24 bytes per value, of 5.9 that
-// two reads and a write stream at; p = 6, 16x16x32 cells, 128 vectors 1.56
+// 2.48 (the table kernel 4.73) = 4.4 TB/s of the 24 bytes per value, of 5.9 that
+// two reads and a write stream at; p = 6, 16x16x32 cells, 128 vectors 1.57
 // (5.53); p = 5, 20x20x40 cells, 200 vectors 3.16 (8.79); p = 3, 24x24x48 cells,
 // 100 vectors 0.50 (1.45); p = 2, 30x30x60 cells, 100 vectors 0.29 (1.09); the
-// Bloch mode on the p = 4 slab with 128 complex vectors 2.53 (7.4, the table kernel
+// Bloch mode on the p = 4 slab with 128 complex vectors 2.55 (7.4, the table kernel
 // with dense k.G products).
 #include <hip/hip_runtime.h>
 

@@ -32,14 +32,17 @@ bool tensor_applies(const fe_mesh *m, const StepArgs &a) {
     return a.alpha != 0.0 && std::isfinite(a.beta / a.alpha);
 }
 
-// Where it is the default.  It is faster than the cell kernels at every size
-// measured, so the line is drawn by what else holds:
-// the default of the other degrees on a few cells, and of one or two vectors
-// up to a mesh of the size where Lanczos and CG spend time on the product,
-// are documented to equal the one-cell kernel (variant 1) bit for bit.  The
-// rule looks at the number of vectors, not of real columns, so that a complex
-// block at the Gamma point takes the kernel of its real and imaginary parts; at
-// other k-points (no such equality there) it has no line.
+// Where it is the default.  The line is not one of speed: it is drawn by what
+// else holds, namely that the default of the other degrees on a few cells, and of
+// one or two vectors up to a mesh of the size where Lanczos and CG spend time on
+// the product, are documented to equal the one-cell kernel (variant 1) bit for
+// bit.  At the line (us per product, cell kernels / this one): 64 cells, 16
+// vectors 34 / 9 at p = 1 and 2, 148 / 23 at p = 5, 311 / 27 at p = 6, 323 / 32 at
+// p = 7; one vector on 1100 cells 42 / 9 (p = 1) to 328 / 44 (p = 7).  Below it the
+// cell kernels' times stand.  The rule looks at the number of vectors, not of
+// real columns, so that a complex block at the Gamma point takes the kernel of its
+// real and imaginary parts; at other k-points (no such equality there) it has no
+// line.
 bool tensor_default(const fe_mesh *m, const StepArgs &a) {
     if (a.S) return true;
     const int64_t vectors = a.vectors ? a.vectors : a.N;
