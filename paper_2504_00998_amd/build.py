@@ -21,7 +21,7 @@ FLAGS = [
     "-ffp-contract=off", "-Wall", "-Wno-unused-result",
 ]
 LIBS = ["-L/opt/rocm/lib", "-lrocblas", "-lrocsolver", "-Wl,-rpath,/opt/rocm/lib"]
-JOBS = int(os.environ.get("MAX_JOBS", "0")) or min(8, os.cpu_count() or 1)
+JOBS = int(os.environ.get("MAX_JOBS") or 0) or min(8, os.cpu_count() or 1)
 
 
 def build(verbose: bool = False) -> str:
